@@ -1,7 +1,7 @@
 // Naive Bayes scoring for more than two classes on the vector ALUs
 // (paper, section 4: the class with the highest posterior wins; here C >= 3,
-// e.g. malware families).  Used for the FP32 table (the plain path) and for
-// BF16 tables with fewer than 16 classes.
+// e.g. malware families), int32 features.  (Byte features, which BF16 operands
+// hold exactly, are scored on the matrix cores: nb_score_tile.hip.)
 //
 // The kernel contracts each file against the P = C class-centred rows
 // W_c - mean_c W (posteriors depend on score differences only; the centred
@@ -9,13 +9,13 @@
 // requested, the aux row mean_c W that restores s_c.  Each lane owns ONE file:
 // all lanes of a wave step through the same feature at the same time, so the
 // table value of (feature, class) is the same for the whole wave and comes
-// from LDS as a broadcast read, while the FMA count per feature byte is the
-// number of rows.  Feature bytes are staged per wave through LDS: a coalesced
-// load of 64 files x 64 bytes, then each lane reads its own file's 64 bytes.
+// from LDS as a broadcast read, while the FMA count per feature is the number
+// of rows.  Features are staged per wave through LDS: a coalesced load of 64
+// files x 16 features, then each lane reads its own file's 64 bytes.
 // The table is staged in LDS in slices of kSlice features, transposed to
-// feature-major.  Sums are two-level: 64-byte sub-steps accumulate into an
-// inner partial that is added to the running total, so no term passes
-// through more than 64 + F/64 roundings (the error depth used by the tests).
+// feature-major.  Sums are two-level: the sub-steps of 16 features accumulate
+// into an inner partial that is added to the running total, so no term passes
+// through more than 16 + F/16 roundings (the error depth used by the tests).
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -57,9 +57,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 // NS: sums per file, >= a.ns (C centred rows, plus the aux row when raw
 // scores are requested; extra sums see zero rows); TS: LDS stride of a
 // feature's table entries (NS rounded up to 4).
-template <int XT, int NS, bool BIN>
+template <int NS, bool BIN>
 __global__ __launch_bounds__(kThreads) void scoreC_kernel(ScoreCArgs a) {
-  constexpr int EB = (XT == NB_X_I32) ? 4 : 1;
+  constexpr int EB = 4;
   constexpr int KS = kStepBytes / EB;          // features per sub-step
   constexpr int TS = (NS + 3) / 4 * 4;
   __shared__ float tbl[kSlice * TS];
@@ -113,36 +113,14 @@ __global__ __launch_bounds__(kThreads) void scoreC_kernel(ScoreCArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) mine[q] = *reinterpret_cast<const dev::u32x4*>(&xs[wave][lane * kXRow + 16 * q]);
         wave_lds_sync();
-        // FP8 bytes past the last feature may encode NaN: clear them
-        const int nvalid = min(KS, a.F - (k0 + ks));
-        if (XT == NB_X_FP8 && nvalid < KS) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const int b0 = 16 * q + 4 * d;
-              const int nb = min(4, max(0, nvalid - b0));
-              mine[q][d] &= (nb >= 4) ? ~0u : ((1u << (8 * nb)) - 1u);
-            }
-        }
         float inner[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) inner[s] = 0.0f;
         const float* tb = tbl + ks * TS;
 #pragma unroll
         for (int e = 0; e < KS; ++e) {
-          float g;
-          if (XT == NB_X_I32) {
-            g = (float)(int32_t)mine[e >> 2][e & 3];
-          } else if (XT == NB_X_U8) {
-            g = (float)((mine[e >> 4][(e >> 2) & 3] >> (8 * (e & 3))) & 0xFFu);
-          } else {
-            const uint32_t w = mine[e >> 4][(e >> 2) & 3];
-            g = ((e & 2) ? __builtin_amdgcn_cvt_pk_f32_fp8(w, true) : __builtin_amdgcn_cvt_pk_f32_fp8(w, false))[e & 1];
-          }
-          // presence: a clamp to [0, 1] for integer counts (folds into the
-          // conversion), a compare for FP8 values
-          if (BIN) g = (XT == NB_X_FP8) ? (g > 0.0f ? 1.0f : 0.0f) : __builtin_amdgcn_fmed3f(g, 0.0f, 1.0f);
+          float g = (float)(int32_t)mine[e >> 2][e & 3];
+          if (BIN) g = __builtin_amdgcn_fmed3f(g, 0.0f, 1.0f);   // presence: a clamp to [0, 1] of integer counts
           const float* te = tb + e * TS;
 #pragma unroll
           for (int s4 = 0; s4 < TS; s4 += 4) {
@@ -198,44 +176,37 @@ __global__ __launch_bounds__(kThreads) void scoreC_kernel(ScoreCArgs a) {
 
 using KernelFn = void (*)(ScoreCArgs);
 
-template <int XT, int NS>
+template <int NS>
 KernelFn pick_bin(bool bin) {
-  return bin ? scoreC_kernel<XT, NS, true> : scoreC_kernel<XT, NS, false>;
+  return bin ? scoreC_kernel<NS, true> : scoreC_kernel<NS, false>;
 }
 
-template <int XT>
 KernelFn pick_ns(int ns, bool bin) {
   // sums per file rounded up to a compiled width (extra rows are zero)
-  if (ns <= 4) return pick_bin<XT, 4>(bin);
-  if (ns <= 8) return pick_bin<XT, 8>(bin);
-  if (ns <= 12) return pick_bin<XT, 12>(bin);
-  if (ns <= 16) return pick_bin<XT, 16>(bin);
-  if (ns <= 17) return pick_bin<XT, 17>(bin);
-  if (ns <= 20) return pick_bin<XT, 20>(bin);
-  if (ns <= 24) return pick_bin<XT, 24>(bin);
-  if (ns <= 32) return pick_bin<XT, 32>(bin);
+  if (ns <= 4) return pick_bin<4>(bin);
+  if (ns <= 8) return pick_bin<8>(bin);
+  if (ns <= 12) return pick_bin<12>(bin);
+  if (ns <= 16) return pick_bin<16>(bin);
+  if (ns <= 17) return pick_bin<17>(bin);
+  if (ns <= 20) return pick_bin<20>(bin);
+  if (ns <= 24) return pick_bin<24>(bin);
+  if (ns <= 32) return pick_bin<32>(bin);
   return nullptr;
 }
 
 }  // namespace
 
-// Entry from nb_score for C >= 3 on the vector ALUs.  Arguments are validated
+// Entry from nb_score for C >= 3 and int32 features.  Arguments are validated
 // by the caller.
-int launch_scoreC_valu(const nb_model* m, const nb_layout& L, const void* x, int32_t xtype, int64_t n, int64_t ld,
-                       int32_t wtype, int32_t* labels, float* log_post, float* scores, hipStream_t s) {
+int launch_scoreC_valu(const nb_model* m, const nb_layout& L, const void* x, int64_t n, int64_t ld, int32_t wtype,
+                       int32_t* labels, float* log_post, float* scores, hipStream_t s) {
   const int C = m->n_classes;
   const int ns = C + (scores ? 1 : 0);
-  KernelFn fn = nullptr;
-  const bool bin = m->kind == NB_BERNOULLI;
-  switch (xtype) {
-    case NB_X_U8: fn = pick_ns<NB_X_U8>(ns, bin); break;
-    case NB_X_I32: fn = pick_ns<NB_X_I32>(ns, bin); break;
-    default: fn = pick_ns<NB_X_FP8>(ns, bin); break;
-  }
+  const KernelFn fn = pick_ns(ns, m->kind == NB_BERNOULLI);
   if (!fn)
     return fail(NB_EINVAL, "vector-ALU scoring supports up to 31 classes (32 with raw scores); "
                            "use the BF16 table (matrix cores) for more");
-  const int eb = elem_bytes(xtype);
+  const int eb = 4;
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);
   ScoreCArgs a;
   a.x = static_cast<const uint8_t*>(x);
