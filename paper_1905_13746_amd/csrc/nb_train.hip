@@ -48,7 +48,12 @@ constexpr int kChunk = 64 * kSeg;         // features per chunk (one wave)
 // features, eight rows of four loads for int32 features
 template <int XT>
 constexpr int batch_rows() { return XT == NB_X_I32 ? 8 : 16; }
-constexpr int64_t kMinRowsPerSlot = 512;
+// Rows of a slot: with two classes one 64-row label window per wave, since a
+// call of few rows is a chain of label and row loads per wave (20,000 files at F
+// = 200: 21.2 us with two windows per wave, 17.4 with one); with more classes a
+// wave's row list spans several windows and shorter slots only cut it (7
+// classes, 50,000 files: 33.7 us against 36.0 with 256 rows).
+constexpr int64_t min_rows_per_slot(int C) { return C == 2 ? 256 : 512; }
 
 struct CountArgs {
   const uint8_t* x;
@@ -76,7 +81,7 @@ struct CountArgs {
 // list in LDS and loads them kBatch at a time, so a batch is short only at the
 // end of a list instead of in every window.
 template <int XT, bool BIN, bool SQ = false, int WIN = 1>
-__global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
+__global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_kernel(CountArgs a) {
   constexpr int EB = (XT == NB_X_I32) ? 4 : 1;   // bytes per feature
   constexpr int NV = EB;                          // 16-byte vectors per lane per row
   constexpr int kBatch = batch_rows<XT>();
@@ -95,9 +100,24 @@ __global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
   const int64_t w_begin = min(r_end, r_begin + wave * per);
   const int64_t w_end = min(r_end, w_begin + per);
 
-  const int f0 = ch * kChunk + lane * kSeg;       // this lane's first feature
-  const int64_t col = (int64_t)f0 * EB;
-  const int64_t chunk_end = (int64_t)min(a.Fp, (ch + 1) * kChunk) * EB;
+  // This lane's features: bytes, 16 consecutive ones (one load); int32, four
+  // groups of four, 256 features apart, so that each of a wave's four loads
+  // reads one contiguous kilobyte of the row (100,000 files of 1,000 int32
+  // features: 107 -> 92 us against 16 consecutive ones per lane).  Groups past
+  // the last feature load nothing (an offset out of range): the rows' own bytes
+  // are all that is read, and only the buffer's last load can cross its end (when
+  // whole 1,024-feature chunks were loaded, the last rows' lanes went byte by
+  // byte, most of the time of a small call: 2,000 files of 64 int32 features 82
+  // us, now 48).
+  auto feature = [&](int e) { return ch * kChunk + (EB == 4 ? 256 * (e / 4) + 4 * lane + e % 4 : lane * kSeg + e); };
+  uint32_t col[NV];
+  bool live[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    live[q] = feature(4 * q) < a.F;
+    col[q] = live[q] ? (uint32_t)feature(4 * q) * EB : dev::kNoAccess;
+  }
+  const int64_t chunk_end = min((int64_t)a.F * EB + 15 & ~(int64_t)15, (int64_t)(ch + 1) * kChunk * EB);
 
   // byte features: packed 16-bit lanes (lo: bytes 0,2; hi: bytes 1,3 of each dword)
   uint32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
@@ -109,7 +129,8 @@ __global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
   for (int e = 0; e < kSeg; ++e) acc[e] = 0;
   int packed_rows = 0;
   int64_t matched = 0;
-  bool bad_label = false, negative = false, too_large = false;
+  bool bad_label = false;
+  uint32_t neg_bits = 0, largest = 0;   // int32 features: OR (sign bit) and maximum of the values
 
   auto flush = [&]() {
     if (SQ) {
@@ -171,30 +192,30 @@ __global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
     }
     // the list is written and read by the same wave, in order
     if (WIN > 1) __builtin_amdgcn_wave_barrier();
-    // every row of the windows (their chunk) lies inside the buffer
+    // every load of the windows' rows lies inside the buffer, at 32-bit offsets
     const int64_t last = min(base + kListRows, w_end) - 1;
-    const bool window_fast =
+    const bool fast =
         last * a.ld_bytes + chunk_end <= a.total_bytes && kListRows * a.ld_bytes < ((int64_t)1 << 31);
     const auto wrsrc = dev::make_rsrc(a.x + base * a.ld_bytes, a.total_bytes - base * a.ld_bytes);
     for (int b = 0; WIN == 1 ? mask != 0 : b < total; b += kBatch) {
-      int64_t rows[kBatch];
+      // the batch's rows, relative to base; slots past cnt repeat its first
+      // row and are zeroed after the loads, which are all issued
+      uint32_t rel[kBatch];
       int cnt = 0;
       if (WIN == 1) {
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
           if (mask) {
-            const int idx = __ffsll((unsigned long long)mask) - 1;
+            rel[k] = (uint32_t)(__ffsll((unsigned long long)mask) - 1);
             mask &= mask - 1;
-            rows[k] = base + idx;
             ++cnt;
           } else {
-            rows[k] = -1;
+            rel[k] = rel[0];
           }
         }
       } else {
         // b is a multiple of kBatch: four aligned 16-byte reads per 16 rows
         cnt = min(kBatch, total - b);
-        uint32_t rel[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; k += 4) {
           const uint4 q4 = *reinterpret_cast<const uint4*>(lst + b + k);
@@ -204,59 +225,59 @@ __global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
           rel[k + 3] = q4.w;
         }
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) rows[k] = (k < cnt) ? base + rel[k] : -1;
+        for (int k = 1; k < kBatch; ++k) rel[k] = (k < cnt) ? rel[k] : rel[0];
       }
       dev::u32x4 v[kBatch][NV];
-      if (window_fast) {
-        // every row of the window is in bounds: one descriptor for the
-        // window, all loads issued unconditionally (slots past cnt re-read
-        // the batch's first row and are zeroed afterwards)
+      auto offset = [&](int k, int q) { return rel[k] * (uint32_t)a.ld_bytes + col[q]; };
+      if (fast) {
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-          const uint32_t ro = (uint32_t)((k < cnt ? rows[k] : rows[0]) - base) * (uint32_t)a.ld_bytes;
+        for (int k = 0; k < kBatch; ++k)
 #pragma unroll
-          for (int q = 0; q < NV; ++q) v[k][q] = load_window(wrsrc, ro + (uint32_t)col + 16 * q);
-        }
+          for (int q = 0; q < NV; ++q) v[k][q] = load_window(wrsrc, offset(k, q));
+      } else {
+        // the buffer's last rows: the load that crosses the buffer's end goes
+        // byte by byte, behind the others (as do all loads of rows whose stride
+        // is beyond a descriptor's offsets)
+        const bool near = kListRows * a.ld_bytes < ((int64_t)1 << 31);
+        const int64_t left = a.total_bytes - base * a.ld_bytes;
+        const uint32_t end = !near ? 0u : (left < ((int64_t)1 << 31) ? (uint32_t)left : 0x7FFFFFFFu);
 #pragma unroll
         for (int k = 0; k < kBatch; ++k)
 #pragma unroll
           for (int q = 0; q < NV; ++q)
-            if (k >= cnt) v[k][q] = dev::u32x4{0u, 0u, 0u, 0u};
-      } else {
+            v[k][q] = load_window(wrsrc, near && offset(k, q) + 16 <= end ? offset(k, q) : dev::kNoAccess);
 #pragma unroll
-      for (int k = 0; k < kBatch; ++k) {
+        for (int k = 0; k < kBatch; ++k)
 #pragma unroll
-        for (int q = 0; q < NV; ++q) v[k][q] = dev::u32x4{0u, 0u, 0u, 0u};
-        if (rows[k] >= 0) {
-          const int64_t row_off = rows[k] * a.ld_bytes;
-          const uint8_t* p = a.x + row_off + col;
-          if (row_off + chunk_end <= a.total_bytes) {
-            // streaming, non-temporal loads through a per-row buffer resource
-            const auto rsrc = dev::make_rsrc(a.x + row_off, a.total_bytes - row_off);
-#pragma unroll
-            for (int q = 0; q < NV; ++q) v[k][q] = dev::buffer_load16(rsrc, (uint32_t)col + 16 * q);
-          } else {
-#pragma unroll
-            for (int q = 0; q < NV; ++q)
-              v[k][q] = dev::load16_guarded(p + 16 * q, a.total_bytes - (row_off + col + 16 * q));
+          for (int q = 0; q < NV; ++q) {
+            const int64_t off = (int64_t)rel[k] * a.ld_bytes + col[q];
+            if (live[q] && off + 16 > (int64_t)end)
+              v[k][q] = dev::load16_guarded(a.x + base * a.ld_bytes + off, left - off);
           }
-        }
       }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k)
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+          if (k >= cnt) v[k][q] = dev::u32x4{0u, 0u, 0u, 0u};
+      if (EB == 4 && (a.F & 3)) {     // the values past the last feature of its group of four
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k)
+#pragma unroll
+          for (int e = 0; e < 4 * NV; ++e)
+            if (feature(e) >= a.F) v[k][e / 4][e % 4] = 0u;
       }
 #pragma unroll
       for (int k = 0; k < kBatch; ++k) {
         if (XT == NB_X_I32) {
+          // a negative value (or, squared, one of 65536 or more) fails the
+          // call, so the sums need only be right without one
 #pragma unroll
-          for (int q = 0; q < NV; ++q) {
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const int e = 4 * q + d;
-              const int32_t val = (int32_t)v[k][q][d];
-              const bool valid = (f0 + e) < a.F;
-              if (valid && val < 0) negative = true;
-              if (SQ && valid && val >= 65536) too_large = true;
-              if (valid) acc[e] += SQ ? (int64_t)val * val : (BIN ? (int64_t)(val > 0) : (int64_t)val);
-            }
+          for (int e = 0; e < 4 * NV; ++e) {
+            const uint32_t val = v[k][e / 4][e % 4];
+            neg_bits |= val;
+            if (SQ) largest = max(largest, val);
+            acc[e % kSeg] += SQ ? (uint32_t)__umul24(val, val) : (BIN ? min(val, 1u) : val);
           }
         } else if (SQ) {
 #pragma unroll
@@ -295,8 +316,8 @@ __global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
 
   {
     const int any_bad = __syncthreads_or(bad_label && cls == 0 && ch == 0);
-    const int any_neg = __syncthreads_or(negative);
-    const int any_big = __syncthreads_or(too_large);
+    const int any_neg = __syncthreads_or((int32_t)neg_bits < 0);
+    const int any_big = __syncthreads_or(SQ && largest >= 65536u);
     if (threadIdx.x == 0)
       a.flag_part[((int64_t)slot * a.C + cls) * gridDim.z + ch] =
           (any_bad ? kFlagBadLabel : 0) | (any_neg ? kFlagNegative : 0) | (any_big ? kFlagOverflow : 0);
@@ -317,9 +338,9 @@ __global__ __launch_bounds__(kThreads) void count_kernel(CountArgs a) {
     for (int w = 0; w < kWaves - 1; ++w)
 #pragma unroll
       for (int e = 0; e < kSeg; ++e) acc[e] += red[w][e][lane];
-    int64_t* dst = a.part + ((int64_t)slot * a.C + cls) * a.Fp + f0;
+    int64_t* dst = a.part + ((int64_t)slot * a.C + cls) * a.Fp;
 #pragma unroll
-    for (int e = 0; e < kSeg; ++e) dst[e] = acc[e];
+    for (int e = 0; e < kSeg; ++e) dst[feature(e)] = acc[e];
     if (ch == 0 && lane == 0)
       a.nc_part[(int64_t)slot * a.C + cls] = red_m[0] + red_m[1] + red_m[2] + red_m[3];
   }
@@ -836,21 +857,33 @@ int count_capacity(int32_t xtype, int win) {
   return resident_per_cu(count_fn(xtype, false, false, win), kThreads, 0) * device_cu_count();
 }
 
-// Row slots of the count pass, with at least kMinRowsPerSlot rows per slot.
+// Row slots of the count pass, with at least min_rows_per_slot rows per slot.
 // Two classes: as many (slot, class, chunk) workgroups as fit on the device
 // in one round (a few more would run as a second, nearly empty round).  With
 // more classes a workgroup's work is the rows of its class in its slot, which
 // differs between classes as much as their priors do; four rounds of smaller
 // slots let the workgroups of the small classes finish and make room, so that
-// the large classes' rows are spread over the whole device.
+// the large classes' rows are spread over the device, and whole row lists of
+// the four waves per slot keep the loads in full batches (16 classes, F = 4096,
+// 200,003 files: 247 -> 239 us; two classes lose by it, 49.5 -> 55.0 us, the
+// longer slots leaving workgroups out).
 constexpr int64_t kManyClassRounds = 4;
-int64_t train_slots(int32_t C, int32_t F, int64_t n, int32_t xtype) {
+struct Slots {
+  int64_t rows, n;       // rows per slot, slots
+};
+Slots train_slots(int32_t C, int32_t F, int64_t n, int32_t xtype) {
   const int64_t nch = (align_up((size_t)F, kFeaturePad)) / kChunk;
   const int64_t units = std::max<int64_t>(1, count_capacity(xtype, count_win(C)));
   const int64_t rounds = C > 2 ? kManyClassRounds : 1;
   const int64_t s = std::max<int64_t>(1, rounds * units / (C * nch));
-  const int64_t by_rows = std::max<int64_t>(1, (n + kMinRowsPerSlot - 1) / kMinRowsPerSlot);
-  return std::max<int64_t>(1, std::min(s, by_rows));
+  const int64_t by_rows = std::max<int64_t>(1, (n + min_rows_per_slot(C) - 1) / min_rows_per_slot(C));
+  const int64_t list = (int64_t)kWaves * 64 * count_win(C);
+  Slots t;
+  t.n = std::max<int64_t>(1, std::min(s, by_rows));
+  t.rows = std::max<int64_t>(1, (n + t.n - 1) / t.n);
+  if (C > 2 && t.rows > list) t.rows = (t.rows + list - 1) / list * list;
+  t.n = std::max<int64_t>(1, (n + t.rows - 1) / t.rows);
+  return t;
 }
 
 // Workspace: per-slot partials, per-slot class totals, and the RS
@@ -1027,7 +1060,7 @@ extern "C" {
 size_t nb_train_workspace_bytes(int32_t n_classes, int32_t n_features, int64_t n, int32_t xtype) {
   nb_layout L;
   if (!compute_layout(n_classes, n_features, &L) || n < 0 || elem_bytes(xtype) == 0) return 0;
-  return train_ws(n_classes, L.padded_features, train_slots(n_classes, n_features, n, xtype)).total;
+  return train_ws(n_classes, L.padded_features, train_slots(n_classes, n_features, n, xtype).n).total;
 }
 
 int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, const int32_t* y,
@@ -1056,10 +1089,9 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
   if ((reinterpret_cast<uintptr_t>(workspace) & 7) != 0) return fail(NB_EINVAL, "workspace must be 8-byte aligned");
 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  uint8_t* base = static_cast<uint8_t*>(m->dev);
-  int32_t* status = reinterpret_cast<int32_t*>(base + L.off_status);
   const int Fp = L.padded_features;
-  const int64_t S = train_slots(C, F, n, xtype);
+  const Slots slots = train_slots(C, F, n, xtype);
+  const int64_t S = slots.n;
   const TrainWs tw = train_ws(C, Fp, S);
   uint8_t* wsb = static_cast<uint8_t*>(workspace);
   int64_t* part = reinterpret_cast<int64_t*>(wsb + tw.off_part);
@@ -1080,7 +1112,7 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
   ca.n = n;
   ca.total_bytes = ((n - 1) * ld + F) * (int64_t)eb;
   ca.y = y;
-  ca.rows_per_slot = (n + S - 1) / S;
+  ca.rows_per_slot = slots.rows;
   ca.part = part;
   ca.nc_part = nc_part;
   ca.flag_part = flag_part;
