@@ -10,12 +10,15 @@
 //                  most 94 bits) shifted up 32 bits, with F - 1 - f in the
 //                  low word: keys are distinct and a larger key is a better
 //                  feature, an exact tie going to the lower index.  A radix
-//                  select (16 passes of 8-bit digits, one LDS histogram per
+//                  select (passes of 8-bit digits, one LDS histogram per
 //                  pass, the digit found by a wave scan) yields the k-th
 //                  largest key; the features at or above it are written in
-//                  ascending order by a ballot compaction.  Keys are
-//                  recomputed from the counts (L2-resident) in every pass,
-//                  so any F works with 1 KB of LDS.
+//                  ascending order by a ballot compaction.  A chain of
+//                  barriers bounds it, so passes count: keys stay in
+//                  registers up to 2,048 features (beyond, they are
+//                  recomputed from the counts in every pass), digits that no
+//                  key has are passed over, and the passes end once the
+//                  prefix decides.
 //   expand_rows    the k-feature model widened to the full feature vector
 //                  (its tables and rows at the selected features, zero
 //                  elsewhere; a binary search of the ascending index list
@@ -80,23 +83,60 @@ __device__ __forceinline__ u128 select_key(const int32_t* __restrict__ counts, i
   return (d << 32) | (uint32_t)(F - 1 - f);
 }
 
+// KR: keys per thread held in registers (F <= 256 KR), or 0: recomputed from
+// the counts in every pass.  The passes run from the top digit that any key of
+// the model has and stop as soon as every key that matches the prefix is wanted;
+// a digit that no key has (the zeros between the differences and the feature
+// indices) is passed over.
+template <int KR>
 __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
   const SelectDesc d = a.d[blockIdx.x];
   const int F = d.F, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int64_t S0 = d.sums[0], S1 = d.sums[1];
   __shared__ uint32_t hist[256];
-  __shared__ uint32_t found[2];
+  __shared__ uint32_t found[3];
   __shared__ uint32_t wcount[4];
+  __shared__ uint32_t ored[4][4];
+
+  u128 keys[KR ? KR : 1];
+  if (KR) {
+#pragma unroll
+    for (int i = 0; i < KR; ++i) keys[i] = (t + 256 * i < F) ? select_key(d.counts, F, t + 256 * i, S0, S1) : 0;
+  }
+  // visit(f, key) for this thread's features
+  auto each = [&](auto visit) {
+    if (KR) {
+#pragma unroll
+      for (int i = 0; i < KR; ++i)
+        if (t + 256 * i < F) visit(keys[i]);
+    } else {
+      for (int f = t; f < F; f += 256) visit(select_key(d.counts, F, f, S0, S1));
+    }
+  };
+  // which digits any key has
+  u128 any = 0;
+  each([&](u128 c) { any |= c; });
+  uint32_t word[4] = {(uint32_t)any, (uint32_t)(any >> 32), (uint32_t)(any >> 64), (uint32_t)(any >> 96)};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) word[i] |= __shfl_xor(word[i], o);
+    if (lane == 0) ored[w][i] = word[i];
+  }
+  __syncthreads();
+  any = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) any |= (u128)(ored[0][i] | ored[1][i] | ored[2][i] | ored[3][i]) << (32 * i);
 
   u128 prefix = 0, mask = 0;
   uint32_t rem = (uint32_t)a.k;  // rank of the wanted key among those matching prefix (1 = largest)
   for (int shift = 120; shift >= 0; shift -= 8) {
+    if (((uint32_t)(any >> shift) & 255u) == 0) continue;   // zero in every key, and so in prefix
     hist[t] = 0;
     __syncthreads();
-    for (int f = t; f < F; f += 256) {
-      const u128 c = select_key(d.counts, F, f, S0, S1);
+    each([&](u128 c) {
       if ((c & mask) == prefix) atomicAdd(&hist[(uint32_t)(c >> shift) & 255u], 1u);
-    }
+    });
     __syncthreads();
     if (w == 0) {
       // lane l holds digits 255 - 4l .. 252 - 4l (descending); an inclusive
@@ -121,24 +161,37 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
           if (run < rem && rem <= run + h[e]) {
             found[0] = (uint32_t)(255 - 4 * lane - e);
             found[1] = rem - run;
+            found[2] = h[e];
           }
           run += h[e];
         }
       }
     }
     __syncthreads();
-    const uint32_t digit = found[0];
     rem = found[1];
-    prefix |= (u128)digit << shift;
+    prefix |= (u128)found[0] << shift;
     mask |= (u128)255u << shift;
+    const bool all = found[2] == rem;   // every key of the bucket is wanted
     __syncthreads();
+    if (all) break;
   }
 
-  // prefix is now the k-th largest key: exactly k features are >= it
+  // exactly k keys are >= prefix (the k-th largest key, or its leading digits)
+  auto at = [&](int f0) {
+    u128 c = 0;
+    if (KR) {
+#pragma unroll
+      for (int i = 0; i < KR; ++i)
+        if (f0 == 256 * i) c = keys[i];
+    } else {
+      c = select_key(d.counts, F, f0 + t, S0, S1);
+    }
+    return c;
+  };
   uint32_t base = 0;
   for (int f0 = 0; f0 < F; f0 += 256) {
     const int f = f0 + t;
-    const bool sel = (f < F) && select_key(d.counts, F, f, S0, S1) >= prefix;
+    const bool sel = (f < F) && at(f0) >= prefix;
     const uint64_t bal = __ballot(sel);
     const uint32_t before = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
     if (lane == 0) wcount[w] = (uint32_t)__popcll(bal);
@@ -462,7 +515,10 @@ int nb_select_features(const nb_model* models, int32_t n_models, int32_t k, int3
     a.n = std::min<int32_t>(kSelectBatch, n_models - m0);
     a.k = k;
     for (int i = 0; i < kSelectBatch; ++i) a.d[i] = desc[(size_t)std::min<int32_t>(m0 + i, n_models - 1)];
-    hipLaunchKernelGGL(select_kernel, dim3((unsigned)a.n), dim3(256), 0, s, a);
+    int32_t most = 0;
+    for (int i = 0; i < a.n; ++i) most = std::max(most, a.d[i].F);
+    const auto fn = most <= 1024 ? select_kernel<4> : (most <= 2048 ? select_kernel<8> : select_kernel<0>);
+    hipLaunchKernelGGL(fn, dim3((unsigned)a.n), dim3(256), 0, s, a);
     NB_HIP_CHECK(hipGetLastError());
   }
   return NB_OK;

@@ -945,6 +945,120 @@ __global__ __launch_bounds__(256) void subset_counts(const int32_t* __restrict__
   }
 }
 
+// A two-class k-feature model (k <= 1024) in one launch of one workgroup: the
+// selected columns, the tables and the scoring rows, which subset_counts,
+// class_tables and form_rows would take three launches for.  Threads 256 c ..
+// 256 c + 255 are class c's workgroup of class_tables (the same expressions and
+// the same order of every sum), the weights meet in LDS for the rows.  Latency
+// and launches bound it: 20 models of 200 features behind their selection took
+// 311 us with three launches each, 183 us with one (and the selection with its
+// keys in registers).
+constexpr int kSubsetMax = 1024;
+struct SubsetArgs {
+  const int32_t* counts;     // [2][F] of the full model
+  const int64_t* totals;     // [2]
+  const int32_t* idx;        // [k]
+  TableArgs t;               // the k-feature model's sections (F = k)
+  float* rows32;
+  uint16_t* rows16;
+  float* row_bias;
+  int32_t* status;
+  int32_t F;
+};
+
+__global__ __launch_bounds__(512) void subset_model2(SubsetArgs a) {
+  constexpr int kPer = kSubsetMax / 256;
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
+  const int k = a.t.F, Fp = a.t.Fp;
+  __shared__ double W[2][kSubsetMax];
+  __shared__ int64_t red_i[2][4];
+  __shared__ double red_d[2][4], bias[2];
+  __shared__ int red_b[2][4];
+  int32_t T[kPer];
+  int64_t sum = 0;
+  bool bad = false;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int j = t + q * 256;
+    T[q] = 0;
+    if (j < k) {
+      const int32_t f = a.idx[j];
+      if (f < 0 || f >= a.F) bad = true;
+      else T[q] = a.counts[(int64_t)c * a.F + f];
+      a.t.counts[(int64_t)c * k + j] = T[q];
+      sum += T[q];
+    }
+  }
+  const int64_t Nc = a.totals[c], N = a.totals[0] + a.totals[1];
+  int any = bad;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    sum += __shfl_xor(sum, m);
+    any |= __shfl_xor(any, m);
+  }
+  if ((t & 63) == 0) {
+    red_i[c][t >> 6] = sum;
+    red_b[c][t >> 6] = any;
+  }
+  __syncthreads();
+  const int64_t Sc = red_i[c][0] + red_i[c][1] + red_i[c][2] + red_i[c][3];
+  const double al = a.t.alpha;
+  const bool multi = a.t.kind == NB_MULTINOMIAL;
+  const double den = multi ? log((double)Sc + al * (double)k) : log((double)Nc + 2.0 * al);
+  double part = 0.0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int j = t + q * 256;
+    if (j < k) {
+      const int64_t i = (int64_t)c * k + j;
+      const double lt = log((double)T[q] + al) - den;
+      double l1 = 0.0;
+      if (!multi) {
+        l1 = log((double)(Nc - T[q]) + al) - den;
+        part += l1;
+      }
+      const double w = multi ? lt : lt - l1;
+      a.t.log_theta[i] = lt;
+      a.t.log_1m_theta[i] = l1;
+      a.t.weight[i] = w;
+      W[c][j] = w;
+    }
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) part += __shfl_xor(part, m);
+  if ((t & 63) == 0) red_d[c][t >> 6] = part;
+  __syncthreads();
+  if (t == 0) {
+    const double lp = log((double)Nc) - log((double)N);
+    const double sum_l1 = red_d[c][0] + red_d[c][1] + red_d[c][2] + red_d[c][3];
+    bias[c] = multi ? lp : lp + sum_l1;
+    a.t.bias[c] = bias[c];
+    a.t.class_totals[c] = Nc;
+    a.t.class_sums[c] = multi ? Sc : Nc;
+  }
+  for (int f = threadIdx.x; f < Fp; f += 512) {
+    const double d = f < k ? W[1][f] - W[0][f] : 0.0, w0 = f < k ? W[0][f] : 0.0;
+    a.rows32[f] = (float)d;
+    a.rows16[f] = f < k ? dev::f64_to_bf16_rne(d) : (uint16_t)0;
+    a.rows32[(int64_t)Fp + f] = (float)w0;
+    a.rows16[(int64_t)Fp + f] = f < k ? dev::f64_to_bf16_rne(w0) : (uint16_t)0;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t flags = 0;
+    for (int g = 0; g < 2; ++g) {
+      if (red_b[g][0] | red_b[g][1] | red_b[g][2] | red_b[g][3]) flags |= kFlagBadIndex;
+      if (a.totals[g] < 1) flags |= kFlagMinFiles;
+    }
+    a.row_bias[0] = (float)(bias[1] - bias[0]);
+    a.row_bias[1] = (float)bias[0];
+    a.status[kStatusFlags] = flags;
+    a.status[kStatusTrained] = (flags == 0) ? 1 : 0;
+    a.status[2] = 0;
+    a.status[3] = 0;
+  }
+}
+
 // Workspace of nb_model_select: part2 [C][Fp], nc2 [C], flags.
 struct SelectWs {
   int32_t n_flags;
@@ -967,6 +1081,25 @@ SelectWs select_ws(int32_t C, int32_t k, int32_t Fp) {
   return w;
 }
 
+// The table kernels' arguments that are the model's own sections and constants.
+TableArgs model_tables(const nb_model* m, const nb_layout& L, double alpha) {
+  uint8_t* base = static_cast<uint8_t*>(m->dev);
+  TableArgs ta = {};
+  ta.counts = reinterpret_cast<int32_t*>(base + L.off_counts);
+  ta.class_totals = reinterpret_cast<int64_t*>(base + L.off_class_totals);
+  ta.class_sums = reinterpret_cast<int64_t*>(base + L.off_class_sums);
+  ta.log_theta = reinterpret_cast<double*>(base + L.off_log_theta);
+  ta.log_1m_theta = reinterpret_cast<double*>(base + L.off_log_1m_theta);
+  ta.weight = reinterpret_cast<double*>(base + L.off_weight);
+  ta.bias = reinterpret_cast<double*>(base + L.off_bias);
+  ta.alpha = alpha;
+  ta.F = m->n_features;
+  ta.C = m->n_classes;
+  ta.Fp = L.padded_features;
+  ta.kind = m->kind;
+  return ta;
+}
+
 // Table build shared by nb_train and nb_model_select: class_tables over RS
 // second-level partials, then the scoring rows and the status word.
 // csum: the class sums from reduce_counts (two classes, multinomial, byte
@@ -975,25 +1108,13 @@ int launch_tables(nb_model* m, const nb_layout& L, const int64_t* part2, const i
                   const int32_t* flag_part, int n_flags, int32_t* class_flags, double alpha, int min_files,
                   hipStream_t s, const int64_t* part2_sq = nullptr, const int64_t* csum = nullptr) {
   uint8_t* base = static_cast<uint8_t*>(m->dev);
-  TableArgs ta;
+  TableArgs ta = model_tables(m, L, alpha);
   ta.part2 = part2;
   ta.nc2 = nc2;
-  ta.counts = reinterpret_cast<int32_t*>(base + L.off_counts);
-  ta.class_totals = reinterpret_cast<int64_t*>(base + L.off_class_totals);
-  ta.class_sums = reinterpret_cast<int64_t*>(base + L.off_class_sums);
-  ta.log_theta = reinterpret_cast<double*>(base + L.off_log_theta);
-  ta.log_1m_theta = reinterpret_cast<double*>(base + L.off_log_1m_theta);
-  ta.weight = reinterpret_cast<double*>(base + L.off_weight);
-  ta.bias = reinterpret_cast<double*>(base + L.off_bias);
   ta.flag_part = flag_part;
   ta.class_flags = class_flags;
   ta.n_flags = n_flags;
-  ta.alpha = alpha;
-  ta.F = m->n_features;
-  ta.C = m->n_classes;
-  ta.Fp = L.padded_features;
   ta.RS = RS;
-  ta.kind = m->kind;
   ta.min_files = min_files;
   if (csum) {
     hipLaunchKernelGGL(tables_rows2, dim3((unsigned)(ta.Fp / 256)), dim3(256), 0, s, ta, csum,
@@ -1195,6 +1316,23 @@ int nb_model_select(const nb_model* full, const int32_t* idx, int32_t k, double 
   int32_t* flag_part = reinterpret_cast<int32_t*>(wsb + w.off_flags);
   int32_t* class_flags = flag_part + w.n_flags;
   const uint8_t* fb = static_cast<const uint8_t*>(full->dev);
+  if (C == 2 && k <= kSubsetMax) {
+    uint8_t* ob = static_cast<uint8_t*>(out->dev);
+    SubsetArgs sa;
+    sa.counts = reinterpret_cast<const int32_t*>(fb + LF.off_counts);
+    sa.totals = reinterpret_cast<const int64_t*>(fb + LF.off_class_totals);
+    sa.idx = idx;
+    sa.t = model_tables(out, L, alpha);
+    sa.rows32 = reinterpret_cast<float*>(ob + L.off_form_f32);
+    sa.rows16 = reinterpret_cast<uint16_t*>(ob + L.off_form_bf16);
+    sa.row_bias = reinterpret_cast<float*>(ob + L.off_form_bias);
+    sa.status = reinterpret_cast<int32_t*>(ob + L.off_status);
+    sa.F = full->n_features;
+    hipLaunchKernelGGL(subset_model2, dim3(1), dim3(512), 0, s, sa);
+    NB_HIP_CHECK(hipGetLastError());
+    if (flags & NB_TRAIN_ASYNC) return NB_OK;
+    return nb_model_status(out, stream);
+  }
   hipLaunchKernelGGL(subset_counts, dim3((unsigned)((k + 255) / 256), (unsigned)C), dim3(256), 0, s,
                      reinterpret_cast<const int32_t*>(fb + LF.off_counts),
                      reinterpret_cast<const int64_t*>(fb + LF.off_class_totals), idx, full->n_features, k,
