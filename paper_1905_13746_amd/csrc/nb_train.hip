@@ -63,16 +63,19 @@ struct CountArgs {
   const int32_t* y;
   int64_t rows_per_slot;
   int64_t* part;           // [S][C][Fp]
+  int64_t* part_sq;        // [S][C][Fp] (SQ)
   int64_t* nc_part;        // [S][C]
   int32_t* flag_part;      // [S][C][chunks] error flags of each workgroup
   int64_t* zero_words;     // n_zero words cleared by workgroup (0, 0, 0), or NULL
   int32_t F, C, Fp, n_zero;
 };
 
-// SQ: sums of squares x^2 instead of counts (the Gaussian variant's second
-// moment): 32-bit per-feature lane sums for byte features (flushed to int64
-// before they can wrap), int64 for int32 features (values of 65536 or more
-// are flagged: their squares could overflow the exact int64 sums).
+// SQ: sums of squares x^2 beside the counts (the Gaussian variant's second
+// moment, from the same pass over the rows): 32-bit per-feature lane sums for
+// byte features (a flush comes every 256 rows, long before they can wrap), int64
+// for int32 features (values of 65536 or more are flagged: their squares could
+// overflow the exact int64 sums).  One pass for both sums takes 36 us where
+// two passes took 35 us each (200,000 files, F = 1000).
 //
 // WIN: 64-row label windows whose matching rows are loaded together.  With
 // WIN = 1 the rows of a batch come straight from the window's ballot mask;
@@ -124,31 +127,32 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
   uint32_t sq32[SQ ? kSeg : 1];
 #pragma unroll
   for (int e = 0; e < (SQ ? kSeg : 1); ++e) sq32[e] = 0;
-  int64_t acc[kSeg];
+  int64_t acc[kSeg], accq[SQ ? kSeg : 1];
 #pragma unroll
   for (int e = 0; e < kSeg; ++e) acc[e] = 0;
+#pragma unroll
+  for (int e = 0; e < (SQ ? kSeg : 1); ++e) accq[e] = 0;
   int packed_rows = 0;
   int64_t matched = 0;
   bool bad_label = false;
   uint32_t neg_bits = 0, largest = 0;   // int32 features: OR (sign bit) and maximum of the values
 
   auto flush = [&]() {
-    if (SQ) {
+    if constexpr (SQ) {
 #pragma unroll
-      for (int e = 0; e < (SQ ? kSeg : 1); ++e) {
-        acc[e] += sq32[e];
+      for (int e = 0; e < kSeg; ++e) {
+        accq[e] += sq32[e];
         sq32[e] = 0;
       }
-    } else {
+    }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[4 * k + 0] += lo[k] & 0xFFFFu;
-        acc[4 * k + 2] += lo[k] >> 16;
-        acc[4 * k + 1] += hi[k] & 0xFFFFu;
-        acc[4 * k + 3] += hi[k] >> 16;
-        lo[k] = 0;
-        hi[k] = 0;
-      }
+    for (int k = 0; k < 4; ++k) {
+      acc[4 * k + 0] += lo[k] & 0xFFFFu;
+      acc[4 * k + 2] += lo[k] >> 16;
+      acc[4 * k + 1] += hi[k] & 0xFFFFu;
+      acc[4 * k + 3] += hi[k] >> 16;
+      lo[k] = 0;
+      hi[k] = 0;
     }
     packed_rows = 0;
   };
@@ -276,17 +280,10 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
           for (int e = 0; e < 4 * NV; ++e) {
             const uint32_t val = v[k][e / 4][e % 4];
             neg_bits |= val;
-            if (SQ) largest = max(largest, val);
-            acc[e % kSeg] += SQ ? (uint32_t)__umul24(val, val) : (BIN ? min(val, 1u) : val);
-          }
-        } else if (SQ) {
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            const uint32_t w = v[k][0][d];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              const uint32_t x = (w >> (8 * b)) & 0xFFu;
-              sq32[(4 * d + b) % (SQ ? kSeg : 1)] += x * x;
+            acc[e % kSeg] += BIN ? min(val, 1u) : val;
+            if constexpr (SQ) {
+              largest = max(largest, val);
+              accq[e % kSeg] += (uint32_t)__umul24(val, val);
             }
           }
         } else {
@@ -300,13 +297,20 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
             }
             lo[d] += l;
             hi[d] += h;
+            if constexpr (SQ) {
+#pragma unroll
+              for (int b = 0; b < 4; ++b) {
+                const uint32_t x = (w >> (8 * b)) & 0xFFu;
+                sq32[4 * d + b] += __umul24(x, x);
+              }
+            }
           }
         }
       }
       if (XT != NB_X_I32) {
-        // packed 16-bit counts hold 256 rows; 32-bit square sums 66,051
+        // packed 16-bit counts hold 256 rows
         packed_rows += cnt;
-        if (packed_rows > (SQ ? 65536 : 256) - kBatch) flush();
+        if (packed_rows > 256 - kBatch) flush();
       }
     }
     // this list's reads are done before the next windows overwrite it
@@ -344,10 +348,27 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
     if (ch == 0 && lane == 0)
       a.nc_part[(int64_t)slot * a.C + cls] = red_m[0] + red_m[1] + red_m[2] + red_m[3];
   }
+  if constexpr (SQ) {     // the squares through the same buffer
+    __syncthreads();
+    if (wave > 0) {
+#pragma unroll
+      for (int e = 0; e < kSeg; ++e) red[wave - 1][e][lane] = accq[e];
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int w = 0; w < kWaves - 1; ++w)
+#pragma unroll
+        for (int e = 0; e < kSeg; ++e) accq[e] += red[w][e][lane];
+      int64_t* dst = a.part_sq + ((int64_t)slot * a.C + cls) * a.Fp;
+#pragma unroll
+      for (int e = 0; e < kSeg; ++e) dst[feature(e)] = accq[e];
+    }
+  }
 }
 
-// First-level reduction of the per-slot partials: grid (ceil(F/64), C, RS),
-// 4 slot lanes x 64 features per workgroup; writes RS second-level partials.
+// First-level reduction of the per-slot partials: grid (ceil(F/64), C, RS), or
+// 2 RS deep with the sums of squares in the upper half; 4 slot lanes x 64 features per workgroup; writes RS second-level partials.
 constexpr int kReduceSplit = 8;
 
 // csum (or NULL): [RS][C] shares of S_c accumulated with integer atomics
@@ -359,8 +380,13 @@ __global__ __launch_bounds__(256) void reduce_counts(const int64_t* __restrict__
                                                     const int64_t* __restrict__ nc_part, int S, int C,
                                                     int F, int Fp, int64_t* __restrict__ part2,
                                                     int64_t* __restrict__ nc2, int64_t* __restrict__ csum,
-                                                    const int32_t* __restrict__ flag_part, int n_flags) {
-  const int c = blockIdx.y, rs = blockIdx.z, RS = gridDim.z;
+                                                    const int32_t* __restrict__ flag_part, int n_flags, int RS,
+                                                    const int64_t* __restrict__ part_sq,
+                                                    int64_t* __restrict__ part2_sq) {
+  const bool squares = (int)blockIdx.z >= RS;
+  const int c = blockIdx.y, rs = squares ? blockIdx.z - RS : blockIdx.z;
+  const int64_t* __restrict__ src = squares ? part_sq : part;
+  int64_t* __restrict__ dst = squares ? part2_sq : part2;
   const int fl = threadIdx.x & 63, sg = threadIdx.x >> 6;
   if (csum) {
     const int64_t nthreads = (int64_t)gridDim.x * gridDim.y * gridDim.z * 256;
@@ -381,13 +407,13 @@ __global__ __launch_bounds__(256) void reduce_counts(const int64_t* __restrict__
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const int kk = k + u * stride;
-        v[u] = (kk < S) ? part[((int64_t)kk * C + c) * Fp + f] : 0;
+        v[u] = (kk < S) ? src[((int64_t)kk * C + c) * Fp + f] : 0;
       }
 #pragma unroll
       for (int u = 0; u < 16; ++u) s += v[u];
     }
   }
-  if (blockIdx.x == 0) {     // class totals: spread over the 64 lanes, then a wave sum
+  if (blockIdx.x == 0 && !squares) {     // class totals: spread over the 64 lanes, then a wave sum
     for (int k = rs * 4 + sg + fl * stride; k < S; k += 64 * stride) m += nc_part[(int64_t)k * C + c];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m += __shfl_xor(m, o);
@@ -399,8 +425,8 @@ __global__ __launch_bounds__(256) void reduce_counts(const int64_t* __restrict__
   __syncthreads();
   if (sg == 0) {
     const int64_t tot = (f < F) ? red[0][fl] + red[1][fl] + red[2][fl] + red[3][fl] : 0;
-    if (f < F) part2[((int64_t)rs * C + c) * Fp + f] = tot;
-    if (blockIdx.x == 0 && fl == 0) nc2[(int64_t)rs * C + c] = redm[0] + redm[1] + redm[2] + redm[3];
+    if (f < F) dst[((int64_t)rs * C + c) * Fp + f] = tot;
+    if (blockIdx.x == 0 && fl == 0 && !squares) nc2[(int64_t)rs * C + c] = redm[0] + redm[1] + redm[2] + redm[3];
     if (csum) {
       int64_t w = tot;
 #pragma unroll
@@ -828,6 +854,143 @@ __global__ __launch_bounds__(256) void gauss_rows(const double* __restrict__ mea
   }
 }
 
+// Two classes: everything between the second-level partials and the status in
+// one launch of one workgroup (class_tables, sumsq_finish, gauss_eps,
+// gauss_tables and gauss_rows are five, each a few microseconds of latency).
+// Threads 256 c .. 256 c + 255 are class c's workgroup of those kernels: the
+// same expressions and the same order of every sum.  14 us at F = 1000, where
+// the five took 26 us and the gaps between them.
+__global__ __launch_bounds__(512) void gauss_tables2(TableArgs a, const int64_t* __restrict__ part2_sq, int64_t* sumsq,
+                                                     double* __restrict__ mean, double* __restrict__ var,
+                                                     double* __restrict__ eps_out, float* __restrict__ mu32,
+                                                     uint16_t* __restrict__ mu16, float* __restrict__ h32,
+                                                     uint16_t* __restrict__ h16, float* __restrict__ row_bias,
+                                                     int32_t* __restrict__ status) {
+  const int c = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
+  const int F = a.F, Fp = a.Fp;
+  __shared__ int64_t red_i[2][4];
+  __shared__ double red_d[2][4], red_m[8], bias[2];
+  __shared__ int red_b[2][4];
+  int32_t bits = 0;
+  for (int i = threadIdx.x; i < a.n_flags; i += 512) bits |= a.flag_part[i];
+  int64_t N[2] = {0, 0};
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int r = 0; r < kReduceSplit; ++r) N[g] += r < a.RS ? a.nc2[(int64_t)r * 2 + g] : 0;
+
+  // ---- the sums: every partial of four features is loaded before any is added
+  constexpr int kPer = 4;
+  int64_t sum = 0;
+  bits &= kFlagOverflow | kFlagBadLabel | kFlagNegative | kFlagBadIndex;
+  for (int f0 = t; f0 < F; f0 += 256 * kPer) {
+    int64_t v[kPer][kReduceSplit], w[kPer][kReduceSplit];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+#pragma unroll
+      for (int r = 0; r < kReduceSplit; ++r) {
+        const int f = f0 + q * 256;
+        const int64_t at = ((int64_t)r * 2 + c) * Fp + f;
+        v[q][r] = (f < F && r < a.RS) ? a.part2[at] : 0;
+        w[q][r] = (f < F && r < a.RS) ? part2_sq[at] : 0;
+      }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      int64_t tot = 0, sq = 0;
+#pragma unroll
+      for (int r = 0; r < kReduceSplit; ++r) {
+        tot += v[q][r];
+        sq += w[q][r];
+      }
+      if (tot > INT32_MAX) {
+        bits |= kFlagOverflow;
+        tot = INT32_MAX;
+      }
+      const int f = f0 + q * 256;
+      if (f < F) {
+        a.counts[(int64_t)c * F + f] = (int32_t)tot;
+        sumsq[(int64_t)c * F + f] = sq;
+        sum += tot;
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    sum += __shfl_xor(sum, m);
+    bits |= __shfl_xor(bits, m);
+  }
+  if ((t & 63) == 0) {
+    red_i[c][t >> 6] = sum;
+    red_b[c][t >> 6] = bits;
+  }
+  __syncthreads();     // and the workgroup's counts and squares are visible to all its threads
+
+  // ---- epsilon
+  const int64_t Nall = N[0] + N[1];
+  double top = 0.0;
+  for (int f = threadIdx.x; f < F; f += 512) {
+    const int64_t tf = (int64_t)a.counts[f] + a.counts[(int64_t)F + f], qf = sumsq[f] + sumsq[(int64_t)F + f];
+    top = fmax(top, u128_to_double(var_numerator(Nall, tf, qf)) / (double)Nall / (double)Nall);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) top = fmax(top, __shfl_xor(top, o));
+  if ((threadIdx.x & 63) == 0) red_m[threadIdx.x >> 6] = top;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) top = fmax(top, red_m[i]);
+  const double eps = 1e-9 * top;
+
+  // ---- tables and rows
+  const int64_t Nc = N[c];
+  const double dn = (double)Nc;
+  double part = 0.0;
+  for (int f = t; f < Fp; f += 256) {
+    double mu = 0.0, h = 0.0;
+    if (f < F) {
+      const int64_t i = (int64_t)c * F + f;
+      const int64_t tf = a.counts[i], qf = sumsq[i];
+      mu = (double)tf / dn;
+      const double v = u128_to_double(var_numerator(Nc, tf, qf)) / dn / dn + eps;
+      h = -0.5 / v;
+      mean[i] = mu;
+      var[i] = v;
+      a.weight[i] = h;
+      part += log(2.0 * M_PI * v);
+    }
+    const int64_t o = (int64_t)c * Fp + f;
+    mu32[o] = (float)mu;
+    mu16[o] = dev::f64_to_bf16_rne(mu);
+    h32[o] = (float)h;
+    h16[o] = dev::f64_to_bf16_rne(h);
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) part += __shfl_xor(part, m);
+  if ((t & 63) == 0) red_d[c][t >> 6] = part;
+  __syncthreads();
+  if (t == 0) {
+    const double s = red_d[c][0] + red_d[c][1] + red_d[c][2] + red_d[c][3];
+    bias[c] = log(dn) - log((double)Nall) - 0.5 * s;
+    a.bias[c] = bias[c];
+    a.class_totals[c] = Nc;
+    a.class_sums[c] = red_i[c][0] + red_i[c][1] + red_i[c][2] + red_i[c][3];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t flags = top > 0.0 ? 0 : kFlagZeroVariance;
+    for (int g = 0; g < 2; ++g) {
+      flags |= red_b[g][0] | red_b[g][1] | red_b[g][2] | red_b[g][3];
+      if (N[g] < a.min_files || N[g] < 1) flags |= kFlagMinFiles;
+    }
+    *eps_out = eps;
+    row_bias[0] = (float)(bias[1] - bias[0]);
+    row_bias[1] = (float)bias[0];
+    status[kStatusFlags] = flags;
+    status[kStatusTrained] = (flags == 0) ? 1 : 0;
+    status[2] = 0;
+    status[3] = 0;
+  }
+}
+
 // 64-row label windows per row list: at least about 32 matching rows per
 // list (two full batches) for 2, 3 to 7 and 8 to 11 classes, about 64 from 12
 // classes on.
@@ -853,8 +1016,8 @@ const void* count_fn(int32_t xtype, bool bin, bool sq, int win) {
 }
 
 // Workgroups of the count kernel resident on the device at once.
-int count_capacity(int32_t xtype, int win) {
-  return resident_per_cu(count_fn(xtype, false, false, win), kThreads, 0) * device_cu_count();
+int count_capacity(int32_t xtype, int win, bool sq) {
+  return resident_per_cu(count_fn(xtype, false, sq, win), kThreads, 0) * device_cu_count();
 }
 
 // Row slots of the count pass, with at least min_rows_per_slot rows per slot.
@@ -871,9 +1034,9 @@ constexpr int64_t kManyClassRounds = 4;
 struct Slots {
   int64_t rows, n;       // rows per slot, slots
 };
-Slots train_slots(int32_t C, int32_t F, int64_t n, int32_t xtype) {
+Slots train_slots(int32_t C, int32_t F, int64_t n, int32_t xtype, bool sq = false) {
   const int64_t nch = (align_up((size_t)F, kFeaturePad)) / kChunk;
-  const int64_t units = std::max<int64_t>(1, count_capacity(xtype, count_win(C)));
+  const int64_t units = std::max<int64_t>(1, count_capacity(xtype, count_win(C), sq));
   const int64_t rounds = C > 2 ? kManyClassRounds : 1;
   const int64_t s = std::max<int64_t>(1, rounds * units / (C * nch));
   const int64_t by_rows = std::max<int64_t>(1, (n + min_rows_per_slot(C) - 1) / min_rows_per_slot(C));
@@ -911,8 +1074,8 @@ TrainWs train_ws(int32_t C, int32_t Fp, int64_t S) {
   // the kind)
   w.off_part_sq = take((size_t)S * C * Fp * 8);
   w.off_part2_sq = take((size_t)w.RS * C * Fp * 8);
-  // count-kernel flags [2][S][C][chunks] (counts, squares), then per-class flags
-  w.off_flags = take(((size_t)2 * S * C * (Fp / kChunk) + C) * 4);
+  // count-kernel flags [S][C][chunks], then per-class flags
+  w.off_flags = take(((size_t)S * C * (Fp / kChunk) + C) * 4);
   // class-sum shares and the flag word of the one-launch two-class tables
   w.off_csum = take((size_t)(w.RS * C + 1) * 8);
   w.total = off;
@@ -1124,6 +1287,18 @@ int launch_tables(nb_model* m, const nb_layout& L, const int64_t* part2, const i
     NB_HIP_CHECK(hipGetLastError());
     return NB_OK;
   }
+  if (m->kind == NB_GAUSSIAN && ta.C == 2) {
+    hipLaunchKernelGGL(gauss_tables2, dim3(1), dim3(512), 0, s, ta, part2_sq,
+                       reinterpret_cast<int64_t*>(base + L.off_sumsq), reinterpret_cast<double*>(base + L.off_mean),
+                       reinterpret_cast<double*>(base + L.off_var), reinterpret_cast<double*>(base + L.off_epsilon),
+                       reinterpret_cast<float*>(base + L.off_form_f32),
+                       reinterpret_cast<uint16_t*>(base + L.off_form_bf16),
+                       reinterpret_cast<float*>(base + L.off_form2_f32),
+                       reinterpret_cast<uint16_t*>(base + L.off_form2_bf16),
+                       reinterpret_cast<float*>(base + L.off_form_bias), reinterpret_cast<int32_t*>(base + L.off_status));
+    NB_HIP_CHECK(hipGetLastError());
+    return NB_OK;
+  }
   hipLaunchKernelGGL(class_tables, dim3((unsigned)ta.C), dim3(256), 0, s, ta);
   NB_HIP_CHECK(hipGetLastError());
   if (m->kind == NB_GAUSSIAN) {
@@ -1211,7 +1386,11 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
 
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int Fp = L.padded_features;
-  const Slots slots = train_slots(C, F, n, xtype);
+  Slots slots = train_slots(C, F, n, xtype);
+  if (m->kind == NB_GAUSSIAN) {   // fewer workgroups fit with the square sums; the workspace holds the larger count
+    const Slots q = train_slots(C, F, n, xtype, true);
+    if (q.n < slots.n) slots = q;
+  }
   const int64_t S = slots.n;
   const TrainWs tw = train_ws(C, Fp, S);
   uint8_t* wsb = static_cast<uint8_t*>(workspace);
@@ -1220,10 +1399,9 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
   int64_t* part2 = reinterpret_cast<int64_t*>(wsb + tw.off_part2);
   int64_t* nc2 = reinterpret_cast<int64_t*>(wsb + tw.off_nc2);
   const bool gauss = (m->kind == NB_GAUSSIAN);
-  const int n_flags1 = (int)(S * C * (Fp / kChunk));
-  const int n_flags = gauss ? 2 * n_flags1 : n_flags1;
+  const int n_flags = (int)(S * C * (Fp / kChunk));
   int32_t* flag_part = reinterpret_cast<int32_t*>(wsb + tw.off_flags);
-  int32_t* class_flags = flag_part + 2 * n_flags1;
+  int32_t* class_flags = flag_part + n_flags;
   int64_t* part_sq = reinterpret_cast<int64_t*>(wsb + tw.off_part_sq);
   int64_t* part2_sq = reinterpret_cast<int64_t*>(wsb + tw.off_part2_sq);
 
@@ -1235,6 +1413,7 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
   ca.y = y;
   ca.rows_per_slot = slots.rows;
   ca.part = part;
+  ca.part_sq = part_sq;
   ca.nc_part = nc_part;
   ca.flag_part = flag_part;
   ca.F = F;
@@ -1251,25 +1430,13 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
   const int win = count_win(C);
   {
     void* args[] = {&ca};
-    NB_HIP_CHECK(hipLaunchKernel(count_fn(xtype, bin, false, win), grid, dim3(kThreads), args, 0, s));
-  }
-  if (gauss) {   // second pass: the sums of squares
-    CountArgs cq = ca;
-    cq.part = part_sq;
-    cq.flag_part = flag_part + n_flags1;
-    void* args[] = {&cq};
-    NB_HIP_CHECK(hipLaunchKernel(count_fn(xtype, false, true, win), grid, dim3(kThreads), args, 0, s));
+    NB_HIP_CHECK(hipLaunchKernel(count_fn(xtype, bin, gauss, win), grid, dim3(kThreads), args, 0, s));
   }
 
-  const dim3 rgrid((unsigned)((F + 63) / 64), (unsigned)C, (unsigned)tw.RS);
+  const dim3 rgrid((unsigned)((F + 63) / 64), (unsigned)C, (unsigned)(gauss ? 2 * tw.RS : tw.RS));
   hipLaunchKernelGGL(reduce_counts, rgrid, dim3(256), 0, s, part, nc_part, (int)S, C, F, Fp, part2, nc2, csum,
-                     flag_part, n_flags);
+                     flag_part, n_flags, (int)tw.RS, part_sq, part2_sq);
   NB_HIP_CHECK(hipGetLastError());
-  if (gauss) {   // (the class totals it writes again are the same values)
-    hipLaunchKernelGGL(reduce_counts, rgrid, dim3(256), 0, s, part_sq, nc_part, (int)S, C, F, Fp, part2_sq, nc2,
-                       nullptr, nullptr, 0);
-    NB_HIP_CHECK(hipGetLastError());
-  }
 
   rc = launch_tables(m, L, part2, nc2, (int)tw.RS, flag_part, n_flags, class_flags, alpha, min_files_per_class,
                      s, part2_sq, csum);
