@@ -55,6 +55,12 @@ constexpr int batch_rows() { return XT == NB_X_I32 ? 8 : 16; }
 // classes, 50,000 files: 33.7 us against 36.0 with 256 rows).
 constexpr int64_t min_rows_per_slot(int C) { return C == 2 ? 256 : 512; }
 
+// The words that reduce_counts adds to with atomics lie on cache lines of their
+// own: 16 classes at F = 4096 send 64 additions to each of 128 words, which took
+// 23.6 us with the words side by side (additions to one line queue) and FILL_SIX
+// apart.
+constexpr int kSumStride = 16;
+
 struct CountArgs {
   const uint8_t* x;
   int64_t ld_bytes;
@@ -66,7 +72,7 @@ struct CountArgs {
   int64_t* part_sq;        // [S][C][Fp] (SQ)
   int64_t* nc_part;        // [S][C]
   int32_t* flag_part;      // [S][C][chunks] error flags of each workgroup
-  int64_t* zero_words;     // n_zero words cleared by workgroup (0, 0, 0), or NULL
+  int64_t* zero_words;     // n_zero words, kSumStride apart, cleared by workgroup (0, 0, 0), or NULL
   int32_t F, C, Fp, n_zero;
 };
 
@@ -95,7 +101,8 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
 
   // the class sums reduce_counts accumulates start from zero (the kernels
   // run in stream order)
-  if (a.zero_words && slot == 0 && cls == 0 && ch == 0 && (int)threadIdx.x < a.n_zero) a.zero_words[threadIdx.x] = 0;
+  if (a.zero_words && slot == 0 && cls == 0 && ch == 0)
+    for (int i = threadIdx.x; i < a.n_zero; i += kThreads) a.zero_words[(int64_t)i * kSumStride] = 0;
   const int64_t r_begin = (int64_t)slot * a.rows_per_slot;
   const int64_t r_end = min(a.n, r_begin + a.rows_per_slot);
   // four contiguous sub-ranges, 64-row aligned
@@ -368,7 +375,8 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
 }
 
 // First-level reduction of the per-slot partials: grid (ceil(F/64), C, RS), or
-// 2 RS deep with the sums of squares in the upper half; 4 slot lanes x 64 features per workgroup; writes RS second-level partials.
+// 2 RS deep with the sums of squares in the upper half; 4 slot lanes x 64
+// features per workgroup; writes RS second-level partials.
 constexpr int kReduceSplit = 8;
 
 // csum (or NULL): [RS][C] shares of S_c accumulated with integer atomics
@@ -394,7 +402,7 @@ __global__ __launch_bounds__(256) void reduce_counts(const int64_t* __restrict__
     for (int64_t i = (((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
          i < n_flags; i += nthreads)
       bits |= flag_part[i];
-    if (bits) atomicOr(reinterpret_cast<int*>(csum + (int64_t)RS * C), bits);
+    if (bits) atomicOr(reinterpret_cast<int*>(csum + (int64_t)RS * C * kSumStride), bits);
   }
   const int f = blockIdx.x * 64 + fl;
   int64_t s = 0, m = 0;
@@ -431,7 +439,9 @@ __global__ __launch_bounds__(256) void reduce_counts(const int64_t* __restrict__
       int64_t w = tot;
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) w += __shfl_xor(w, o);
-      if (fl == 0) atomicAdd(reinterpret_cast<unsigned long long*>(csum + (int64_t)rs * C + c), (unsigned long long)w);
+      if (fl == 0)
+        atomicAdd(reinterpret_cast<unsigned long long*>(csum + ((int64_t)rs * C + c) * kSumStride),
+                  (unsigned long long)w);
     }
   }
 }
@@ -651,7 +661,9 @@ __global__ __launch_bounds__(256) void tables_rows2(TableArgs a, const int64_t* 
   const int f = blockIdx.x * 256 + t;
   const int F = a.F, Fp = a.Fp;
   // the OR of the count kernel's flags, gathered by reduce_counts
-  const int32_t fl = (blockIdx.x == 0 && t == 0) ? *reinterpret_cast<const int32_t*>(csum + (int64_t)a.RS * 2) : 0;
+  const int32_t fl = (blockIdx.x == 0 && t == 0)
+                         ? *reinterpret_cast<const int32_t*>(csum + (int64_t)a.RS * 2 * kSumStride)
+                         : 0;
   int64_t v[2][kReduceSplit], w[2][kReduceSplit], u[2][kReduceSplit];
 #pragma unroll
   for (int c = 0; c < 2; ++c)
@@ -659,7 +671,7 @@ __global__ __launch_bounds__(256) void tables_rows2(TableArgs a, const int64_t* 
     for (int r = 0; r < kReduceSplit; ++r) {
       v[c][r] = (f < F && r < a.RS) ? a.part2[((int64_t)r * 2 + c) * Fp + f] : 0;
       w[c][r] = (r < a.RS) ? a.nc2[(int64_t)r * 2 + c] : 0;
-      u[c][r] = (r < a.RS) ? csum[(int64_t)r * 2 + c] : 0;
+      u[c][r] = (r < a.RS) ? csum[((int64_t)r * 2 + c) * kSumStride] : 0;
     }
   int64_t Tc[2], Nc[2], Sc[2];
 #pragma unroll
@@ -715,6 +727,96 @@ __global__ __launch_bounds__(256) void tables_rows2(TableArgs a, const int64_t* 
       }
       row_bias[0] = (float)(bias[1] - bias[0]);
       row_bias[1] = (float)bias[0];
+      status[kStatusFlags] = flags;
+      status[kStatusTrained] = (flags == 0) ? 1 : 0;
+      status[2] = 0;
+      status[3] = 0;
+    }
+  }
+}
+
+// Three or more classes, multinomial, byte features: as tables_rows2, with a
+// workgroup per 16 features and 16 threads per feature that take the classes in
+// turn, so that C F logarithms spread over the device (class_tables has one
+// workgroup per class); the weights of a feature meet in LDS for the class mean,
+// summed in class order as in form_rows.  16 classes at F = 4096: 5.0 us
+// where class_tables and form_rows took 22 + 9.  grid (Fp / 16).
+__global__ __launch_bounds__(256) void tables_rowsC(TableArgs a, const int64_t* __restrict__ csum,
+                                                    float* __restrict__ rows32, uint16_t* __restrict__ rows16,
+                                                    float* __restrict__ row_bias, int32_t* __restrict__ status) {
+  const int t = threadIdx.x, fl = t & 15, cl = t >> 4;
+  const int F = a.F, Fp = a.Fp, C = a.C;
+  const int f = blockIdx.x * 16 + fl;
+  __shared__ double W[kMaxClasses][16];
+  const double al = a.alpha;
+  for (int c = cl; c < C; c += 16) {
+    int64_t v[kReduceSplit], u[kReduceSplit];
+#pragma unroll
+    for (int r = 0; r < kReduceSplit; ++r) {
+      v[r] = (f < F && r < a.RS) ? a.part2[((int64_t)r * C + c) * Fp + f] : 0;
+      u[r] = (r < a.RS) ? csum[((int64_t)r * C + c) * kSumStride] : 0;
+    }
+    int64_t T = 0, Sc = 0;
+#pragma unroll
+    for (int r = 0; r < kReduceSplit; ++r) {
+      T += v[r];
+      Sc += u[r];
+    }
+    if (f < F) {
+      const double den = log((double)Sc + al * (double)F);
+      const double lt = log((double)T + al) - den;
+      const int64_t i = (int64_t)c * F + f;
+      a.counts[i] = (int32_t)T;
+      a.log_theta[i] = lt;
+      a.log_1m_theta[i] = 0.0;
+      a.weight[i] = lt;
+      W[c][fl] = lt;
+    }
+    if (blockIdx.x == 0 && fl == 0) a.class_sums[c] = Sc;
+  }
+  __syncthreads();
+  double m = 0.0;
+  if (f < F) {
+    for (int c = 0; c < C; ++c) m += W[c][fl];
+    m /= (double)C;
+  }
+  for (int c = cl; c <= C; c += 16) {
+    const double v = f >= F ? 0.0 : (c < C ? W[c][fl] - m : m);
+    rows32[(int64_t)c * Fp + f] = (float)v;
+    rows16[(int64_t)c * Fp + f] = f < F ? dev::f64_to_bf16_rne(v) : (uint16_t)0;
+  }
+  if (blockIdx.x == 0) {
+    __shared__ int64_t N[kMaxClasses];
+    __shared__ double bias[kMaxClasses];
+    if (t < C) {
+      int64_t n = 0;
+#pragma unroll
+      for (int r = 0; r < kReduceSplit; ++r) n += (r < a.RS) ? a.nc2[(int64_t)r * C + t] : 0;
+      N[t] = n;
+      a.class_totals[t] = n;
+    }
+    __syncthreads();
+    if (t < C) {
+      int64_t all = 0;
+      for (int c = 0; c < C; ++c) all += N[c];
+      bias[t] = log((double)N[t]) - log((double)all);
+      a.bias[t] = bias[t];
+    }
+    __syncthreads();
+    double mb = 0.0;
+    for (int c = 0; c < C; ++c) mb += bias[c];
+    mb /= (double)C;
+    if (t < C) row_bias[t] = (float)(bias[t] - mb);
+    if (t == 0) {
+      row_bias[C] = (float)mb;
+      const int32_t bits = *reinterpret_cast<const int32_t*>(csum + (int64_t)a.RS * C * kSumStride) &
+                           (kFlagOverflow | kFlagBadLabel | kFlagNegative | kFlagBadIndex);
+      int32_t flags = 0;
+      for (int c = 0; c < C; ++c) {
+        const int32_t cf = bits | ((N[c] < a.min_files || N[c] < 1) ? kFlagMinFiles : 0);
+        a.class_flags[c] = cf;
+        flags |= cf;
+      }
       status[kStatusFlags] = flags;
       status[kStatusTrained] = (flags == 0) ? 1 : 0;
       status[2] = 0;
@@ -1076,8 +1178,8 @@ TrainWs train_ws(int32_t C, int32_t Fp, int64_t S) {
   w.off_part2_sq = take((size_t)w.RS * C * Fp * 8);
   // count-kernel flags [S][C][chunks], then per-class flags
   w.off_flags = take(((size_t)S * C * (Fp / kChunk) + C) * 4);
-  // class-sum shares and the flag word of the one-launch two-class tables
-  w.off_csum = take((size_t)(w.RS * C + 1) * 8);
+  // class-sum shares and the flag word of the one-launch tables
+  w.off_csum = take((size_t)(w.RS * C + 1) * kSumStride * 8);
   w.total = off;
   return w;
 }
@@ -1265,8 +1367,8 @@ TableArgs model_tables(const nb_model* m, const nb_layout& L, double alpha) {
 
 // Table build shared by nb_train and nb_model_select: class_tables over RS
 // second-level partials, then the scoring rows and the status word.
-// csum: the class sums from reduce_counts (two classes, multinomial, byte
-// features): the tables and rows then take one launch.
+// csum: the class sums from reduce_counts (multinomial, byte features): the
+// tables and rows then take one launch.
 int launch_tables(nb_model* m, const nb_layout& L, const int64_t* part2, const int64_t* nc2, int RS,
                   const int32_t* flag_part, int n_flags, int32_t* class_flags, double alpha, int min_files,
                   hipStream_t s, const int64_t* part2_sq = nullptr, const int64_t* csum = nullptr) {
@@ -1280,7 +1382,8 @@ int launch_tables(nb_model* m, const nb_layout& L, const int64_t* part2, const i
   ta.RS = RS;
   ta.min_files = min_files;
   if (csum) {
-    hipLaunchKernelGGL(tables_rows2, dim3((unsigned)(ta.Fp / 256)), dim3(256), 0, s, ta, csum,
+    hipLaunchKernelGGL(ta.C == 2 ? tables_rows2 : tables_rowsC, dim3((unsigned)(ta.Fp / (ta.C == 2 ? 256 : 16))),
+                       dim3(256), 0, s, ta, csum,
                        reinterpret_cast<float*>(base + L.off_form_f32),
                        reinterpret_cast<uint16_t*>(base + L.off_form_bf16),
                        reinterpret_cast<float*>(base + L.off_form_bias), reinterpret_cast<int32_t*>(base + L.off_status));
@@ -1419,9 +1522,9 @@ int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, c
   ca.F = F;
   ca.C = C;
   ca.Fp = Fp;
-  // two classes, multinomial, byte features: the class sums come from
-  // reduce_counts and the tables and rows take one launch
-  const bool fused = (C == 2 && m->kind == NB_MULTINOMIAL && xtype == NB_X_U8);
+  // multinomial, byte features: the class sums come from reduce_counts and the
+  // tables and rows take one launch
+  const bool fused = (m->kind == NB_MULTINOMIAL && xtype == NB_X_U8);
   int64_t* csum = fused ? reinterpret_cast<int64_t*>(wsb + tw.off_csum) : nullptr;
   ca.zero_words = csum;
   ca.n_zero = fused ? (int)(tw.RS * C + 1) : 0;
