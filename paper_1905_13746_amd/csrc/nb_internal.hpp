@@ -64,10 +64,7 @@ int resident_per_cu(const void* fn, int threads, size_t lds);
 int check_score_args(const nb_model* m, nb_layout* L, const void* x, int32_t xtype, int64_t n, int64_t ld,
                      int32_t wtype, const int32_t* labels, const float* log_post, const float* scores);
 
-// Scoring launchers for more than two classes (arguments validated by nb_score):
-// int32 features on the vector ALUs, byte features on the matrix cores.
-int launch_scoreC_valu(const nb_model* m, const nb_layout& L, const void* x, int64_t n, int64_t ld, int32_t wtype,
-                       int32_t* labels, float* log_post, float* scores, hipStream_t s);
+// Scoring launchers for more than two classes (arguments validated by nb_score).
 bool score16_staged(const nb_model* m, const nb_layout& L, int32_t wtype, const float* scores);
 int launch_score16_staged(const nb_model* m, const nb_layout& L, const void* x, int32_t xtype, int64_t n, int64_t ld,
                           int32_t* labels, float* log_post, hipStream_t s);

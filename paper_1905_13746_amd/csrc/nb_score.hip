@@ -100,19 +100,20 @@ int launch_score2(const nb_model* m, const nb_layout& L, const void* x, int32_t 
   return NB_OK;
 }
 
-// Limits of the byte-feature paths for more than two classes: the FP32 table
-// takes 32 score rows, the BF16 table 256, and the rows that one resource
-// descriptor spans must stay below 2 GiB.
-int check_score_bytes(const nb_model* m, int64_t ld, int32_t wtype, const float* scores) {
+// Limits of the paths for more than two classes: the FP32 table and int32
+// features take 32 score rows, byte features on the BF16 table 256, and the rows
+// that one resource descriptor spans must stay below 2 GiB.
+int check_score_rows(const nb_model* m, int32_t xtype, int64_t ld, int32_t wtype, const float* scores) {
   const int ns = m->n_classes + (scores ? 1 : 0);
-  const bool few = wtype == NB_W_F32 || m->n_classes < 16;
+  const bool few = wtype == NB_W_F32 || m->n_classes < 16 || xtype == NB_X_I32;
   if (few && ns > 32)
-    return fail(NB_EINVAL, "scoring with the FP32 table supports up to 32 classes (31 with raw scores); "
-                           "use the BF16 table for more");
+    return fail(NB_EINVAL, "scoring with the FP32 table or int32 features supports up to 32 classes (31 with raw "
+                           "scores); use byte features with the BF16 table for more");
   if (ns > 256)
     return fail(NB_EINVAL, "matrix-core scoring supports up to 256 score columns (255 classes with raw scores)");
   const int64_t rows = few ? 64 : (ns > 64 ? 128 : 256);
-  if (rows * ld >= ((int64_t)1 << 31)) return fail(NB_EINVAL, "row stride too large (a tile of rows must span < 2 GiB)");
+  if (rows * ld * elem_bytes(xtype) >= ((int64_t)1 << 31))
+    return fail(NB_EINVAL, "row stride too large (a tile of rows must span < 2 GiB)");
   return NB_OK;
 }
 
@@ -150,12 +151,11 @@ extern "C" int nb_score(const nb_model* m, const void* x, int32_t xtype, int64_t
   if (m->kind == NB_GAUSSIAN && (m->n_classes != 2 || xtype == NB_X_FP8))
     return fail(NB_EINVAL, "Gaussian models score two classes with uint8 or int32 features");
   if (m->n_classes == 2) return launch_score2(m, L, x, xtype, n, ld, wtype, labels, log_post, scores, s);
-  // byte features: the matrix cores, whatever the class count and the table
-  // (nb_score_tile.hip, nb_score_mfma.hip); int32 features, which a BF16
-  // operand does not hold, go to the vector ALUs
-  if (xtype == NB_X_I32) return launch_scoreC_valu(m, L, x, n, ld, wtype, labels, log_post, scores, s);
-  rc = check_score_bytes(m, ld, wtype, scores);
+  rc = check_score_rows(m, xtype, ld, wtype, scores);
   if (rc) return rc;
-  if (score16_staged(m, L, wtype, scores)) return launch_score16_staged(m, L, x, xtype, n, ld, labels, log_post, s);
+  // three or more classes: the matrix cores (16 classes on the BF16 table have a
+  // kernel of their own)
+  if (xtype != NB_X_I32 && score16_staged(m, L, wtype, scores))
+    return launch_score16_staged(m, L, x, xtype, n, ld, labels, log_post, s);
   return launch_score_tile(m, L, x, xtype, n, ld, wtype, labels, log_post, scores, s);
 }

@@ -1,6 +1,6 @@
-// Naive Bayes scoring of byte features for more than two classes on the
-// matrix cores (paper, section 4: the class with the highest posterior wins;
-// here C >= 3, e.g. malware families), with the FP32 or the BF16 table.
+// Naive Bayes scoring for more than two classes on the matrix cores (paper,
+// section 4: the class with the highest posterior wins; here C >= 3, e.g. malware
+// families), with the FP32 or the BF16 table.
 //
 // s[file, class] = sum_f g(x_f) W[class, f] is a skinny GEMM (M = files, N =
 // classes, K = features).  Byte counts and FP8-e4m3 values are exact in BF16.
@@ -10,24 +10,27 @@
 // give what an FP32 multiply-add gives: every product is exact and the sums
 // round in FP32.  The vector ALUs need C + 1 operations per feature byte, which
 // held 16 classes at 0.85 TB/s of features; three MFMAs per 16 classes cost a
-// quarter of the matrix cores' time at the rate HBM delivers the bytes.
+// quarter of the matrix cores' time at the rate HBM delivers the bytes.  int32
+// features go through v_mfma_f32_16x16x4_f32 (FP32 products and sums, a third of
+// the matrix cores' time at that rate), four of them per 16-byte load.
 //
 // What bounds it is HBM, and the LDS behind it: 16 files share each table read,
 // so the FP32 table's three parts cost 6 bytes of LDS traffic per feature byte
 // beside the 2 of the transpose (of about 13 per byte that the CUs' LDS delivers
 // at 6 TB/s); 32 files per unit halve that but leave one wave per SIMD the
 // registers, and measured slower (415 against 345 us).  A wave's unit is 16
-// files x KS features, loaded as KS contiguous bytes of each file (512 where the
+// files x KB bytes, loaded as KB contiguous bytes of each file (512 where the
 // table leaves room: 256-byte runs took 415 us for the same files), one unit
 // ahead in registers, and transposed through the wave's private LDS stage, SS
-// features at a time, into the operand layout.  The table of a KS-feature slice
+// bytes at a time, into the operand layout.  The table of a slice's features
 // is split into its BF16 parts while it is staged in LDS, two slices deep: a
 // workgroup walks the slices with PT units of files per wave, so a slice is
 // staged once per 16 PT files of each of its waves.  A table of at most two
 // slices stays in LDS and the waves run without barriers.
 //
-// Measured (us; byte features; before: vector ALUs for the FP32 table and for
-// fewer than 16 classes, a matrix-core kernel on 64-byte loads for the rest):
+// Measured (us; byte features but for the last three; before: vector ALUs for
+// the FP32 table, int32 features and fewer than 16 classes, a matrix-core kernel
+// on 64-byte loads for the rest):
 //   FP32, 16 classes, F = 4096, 400,003 files        1,718 ->  354  (4.6 TB/s)
 //   the same with raw scores                         1,980 ->  378
 //   FP32, 20 classes, F = 2000, 300,000 files          905 ->  204
@@ -35,10 +38,13 @@
 //   FP32, 16 classes, F = 1000, 2,000 files            128 ->   13
 //   BF16, 40 classes, F = 1000, 400,001 files, scores  214 ->  127
 //   BF16, 100 classes, F = 2000, 150,000 files         354 ->  154
+//   int32, 7 classes, F = 2964, 67,476 files, scores   645 ->  230
+//   int32, 16 classes, F = 1792, 111,607 files         484 ->  180
+//   int32, 24 classes, F = 1000, 100,000 files         887 ->  158
 //
-// Sums: the products of 128 consecutive features go to fresh accumulators
-// (leading parts and lower parts apart), whose sum is added to the file's
-// running totals: a term passes through few roundings, and the order depends on
+// Sums: the products of 128 consecutive features (16 int32 ones) go to fresh
+// accumulators (leading parts and lower parts apart), whose sum is added to the
+// file's running totals: a term passes through few roundings, and the order depends on
 // the feature index alone.
 #include <algorithm>
 #include <type_traits>
@@ -49,8 +55,8 @@
 namespace nb {
 namespace {
 
-constexpr int kWindow = 64;      // features per 16-byte load of the operand layout
-constexpr int kFlush = 128;      // features per fresh accumulator
+constexpr int kWindow = 64;      // bytes of a file per 16-byte load of the operand layout
+constexpr int kFlush = 128;      // byte features per fresh accumulator
 
 struct ScoreTileArgs {
   const uint8_t* x;
@@ -96,27 +102,34 @@ __device__ __forceinline__ void argmax_step(float& m, int& best) {
 }
 
 // NT: 16-class column tiles.  NP: BF16 parts of a table entry (3: FP32 table,
-// 1: BF16 table).  MT: 16-file tiles of a unit.  PT: units per wave of a wide
-// workgroup tile (even: the two load buffers alternate).  KS: features per
-// slice.  NW: waves.  AUX: the raw scores' aux row, which would need a column
+// 1: BF16 table; int32 features: entries are staged in FP32 from either).  MT:
+// 16-file tiles of a unit.  PT: units per wave of a wide workgroup tile (even:
+// the two load buffers alternate).  KB: bytes per file of a slice.  SS: bytes per
+// file of the stage.  NW: waves.  AUX: the raw scores' aux row, which would need a column
 // tile of its own, is contracted on the vector ALUs (one FMA per byte, a
 // quarter of a lane's operations) from the FP32 values at hand.
-template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KS, int SS, int NW, bool AUX>
+template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX>
 __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
-  static_assert(PT % 2 == 0 && SS % kFlush == 0 && KS % SS == 0 && 1024 % KS == 0, "tile shape");
+  constexpr bool I32 = XT == NB_X_I32;
+  constexpr int EB = I32 ? 4 : 1;           // bytes per feature
+  constexpr int KS = KB / EB;               // features per slice
+  constexpr int WF = kWindow / EB;          // features per window
+  static_assert(PT % 2 == 0 && SS % kFlush == 0 && KB % SS == 0 && 1024 % KB == 0, "tile shape");
   constexpr int kThreads = 64 * NW;
   constexpr int GF = 16 * MT;               // files per unit
   constexpr int NG = SS / 16;               // granules per file of the stage
   constexpr int FPI = 1024 / SS;            // files per wave load instruction
   constexpr int NLS = GF / FPI;             // loads per lane per stage
-  constexpr int NL = KS / SS * NLS;         // loads per lane per unit
-  constexpr int GPR = KS / 8;               // table granules (8 entries) per row of a slice
+  constexpr int NL = KB / SS * NLS;         // loads per lane per unit
+  constexpr int TE = I32 ? 4 : 8;           // table entries per granule: FP32 or BF16
+  constexpr int GPR = KS / TE;              // table granules per row of a slice
   constexpr int kPart = 16 * NT * GPR;      // granules of one part of a slice
-  constexpr int kSlice = NP * kPart;
-  constexpr int kAcc = NP == 3 ? 2 : 1;     // accumulators: leading parts, lower parts
+  constexpr int NPS = I32 ? 1 : NP;         // parts staged
+  constexpr int kSlice = NPS * kPart;
+  constexpr int kAcc = NPS == 3 ? 2 : 1;     // accumulators: leading parts, lower parts
   constexpr int TG = (kPart + kThreads - 1) / kThreads;   // table granules staged per thread
   constexpr bool kWhole = kPart % kThreads == 0;           // else the last ones are absent
-  extern __shared__ __attribute__((aligned(16))) dev::u32x4 lds4[];   // [2][NP][16 NT][GPR], the stages, AUX: [2][KS] floats
+  extern __shared__ __attribute__((aligned(16))) dev::u32x4 lds4[];   // [2][NPS][16 NT][GPR], the stages, AUX: [2][KS] floats
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -125,12 +138,13 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
   const int col = lane & 15, q = lane >> 4;
   const int lr = lane / NG, lp = lane % NG;
   const int64_t ld = a.ld_bytes;
-  const int nsl = (a.F + KS - 1) / KS;
+  const int nsl = (a.F + KS - 1) / KS, row_bytes = a.F * EB;
   const bool resident = nsl <= 2;
 
   // ---- table slices
   const auto trsrc = dev::make_rsrc(a.rows, (int64_t)a.ns * a.Fp * (NP == 3 ? 4 : 2));   // rows >= ns read as zero
-  constexpr int TV = (NP == 3) ? 2 : 1;     // 16-byte loads per granule
+  constexpr int SE = NP == 3 ? 4 : 2;       // bytes of a source entry
+  constexpr int TV = (TE * SE + 15) / 16;   // loads per granule (16 bytes; 8 for four BF16 entries)
   constexpr int TA = AUX ? (KS + kThreads - 1) / kThreads : 1;
   const auto arsrc = dev::make_rsrc(static_cast<const uint8_t*>(a.rows) + (int64_t)a.C * a.Fp * (NP == 3 ? 4 : 2),
                                     AUX ? (int64_t)a.Fp * (NP == 3 ? 4 : 2) : 0);
@@ -148,11 +162,16 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
 #pragma unroll
     for (int i = 0; i < TG; ++i) {
       const int g = kWhole ? tid + i * kThreads : min(tid + i * kThreads, kPart - 1), r = g / GPR, p = g % GPR;
-      const uint32_t e = (uint32_t)(r * a.Fp + s * KS + 8 * p);
+      const uint32_t e = (uint32_t)(r * a.Fp + s * KS + TE * p);
 #pragma unroll
       for (int v = 0; v < TV; ++v) {
-        const auto w = __builtin_amdgcn_raw_buffer_load_b128(trsrc, (int)(e * (NP == 3 ? 4 : 2) + 16 * v), 0, 0);
-        t[i][v] = dev::u32x4{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+        if constexpr (TE * SE == 8) {
+          const auto w = __builtin_amdgcn_raw_buffer_load_b64(trsrc, (int)(e * SE), 0, 0);
+          t[i][v] = dev::u32x4{(uint32_t)w[0], (uint32_t)w[1], 0u, 0u};
+        } else {
+          const auto w = __builtin_amdgcn_raw_buffer_load_b128(trsrc, (int)(e * SE + 16 * v), 0, 0);
+          t[i][v] = dev::u32x4{(uint32_t)w[0], (uint32_t)w[1], (uint32_t)w[2], (uint32_t)w[3]};
+        }
       }
     }
   };
@@ -170,7 +189,9 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
       // (absent granules repeat the last one)
       const int g = kWhole ? tid + i * kThreads : min(tid + i * kThreads, kPart - 1), r = g / GPR, p = g % GPR;
       const int at = r * GPR + (p ^ (r & 15));
-      if constexpr (NP == 1) {
+      if constexpr (I32 && NP == 1) {       // BF16 entries widened: exact
+        dst[at] = dev::u32x4{t[i][0][0] << 16, t[i][0][0] & 0xFFFF0000u, t[i][0][1] << 16, t[i][0][1] & 0xFFFF0000u};
+      } else if constexpr (NPS == 1) {
         dst[at] = t[i][0];
       } else {
         // leading 8 significant bits, the next 8, the rest (at most 8): each
@@ -206,7 +227,8 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
   // window u of file col sits at lane part u % kRW.  Table reads: granule 8 u +
   // 2 q + h of row col at lane part (u % 2, h).
   constexpr int kRW = NG >= 16 ? 4 : 2;
-  int wpos[16 / FPI], rpos[kRW], tpos[2][2];
+  constexpr int kBlock = I32 ? kWindow : kFlush;   // bytes per fresh accumulator (16 int32 features)
+  int wpos[16 / FPI], rpos[kRW], tpos[2][2], tpos4[4];
 #pragma unroll
   for (int j = 0; j < 16 / FPI; ++j) wpos[j] = stage_granule<NG>(FPI * j + lr, lp);
 #pragma unroll
@@ -215,6 +237,8 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
   for (int w = 0; w < 2; ++w)
 #pragma unroll
     for (int h = 0; h < 2; ++h) tpos[w][h] = col * GPR + ((8 * w + 2 * q + h) ^ col);
+#pragma unroll
+  for (int w = 0; w < 4; ++w) tpos4[w] = col * GPR + ((4 * w + q) ^ col);    // int32: granule 4 u + q
   float bias[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) bias[nt] = (16 * nt + col < a.ns) ? a.row_bias[16 * nt + col] : 0.0f;
@@ -237,82 +261,110 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
         xv[mt] = (stg + rpos[u % kRW])[(16 * mt) * NG + u % (SS / kWindow) / kRW * 4 * kRW];
     };
 #pragma unroll
-    for (int b = 0; b < KS / kFlush; ++b) {
+    for (int b = 0; b < KB / kBlock; ++b) {
       // the last slice of a row: what holds no features is left out, by halves
       // (a branch at every sum made full slices 3% slower; with the aux row's
       // registers it is the cheaper form: 378 against 394 us)
-      constexpr int kSkip = AUX ? 1 : KS / kFlush / 2;
-      if (b > 0 && b % kSkip == 0 && s * KS + b * kFlush >= a.F) break;
-      if (b % (SS / kFlush) == 0) {
+      constexpr int kSkip = AUX || KB == kBlock ? 1 : KB / kBlock / 2;
+      if (b > 0 && b % kSkip == 0 && s * KB + b * kBlock >= row_bytes) break;
+      if (b % (SS / kBlock) == 0) {
         // the operand reads of what the stage held are done before it is
         // rewritten: LDS operations of a wave complete in order
 #pragma unroll
         for (int j = 0; j < NLS; ++j)
-          (stg + wpos[j % (16 / FPI)])[j / (16 / FPI) * 16 * NG] = src[b / (SS / kFlush) * NLS + j];
+          (stg + wpos[j % (16 / FPI)])[j / (16 / FPI) * 16 * NG] = src[b / (SS / kBlock) * NLS + j];
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        read_window(b * (kFlush / kWindow));
+        read_window(b * (kBlock / kWindow));
       }
       f32x4 acc[kAcc][MT][NT];
 #pragma unroll
       for (int h = 0; h < kAcc; ++h) zero(acc[h]);
       float aacc[MT] = {};
 #pragma unroll
-      for (int w = 0; w < kFlush / kWindow; ++w) {
+      for (int w = 0; w < kBlock / kWindow; ++w) {
         // the table reads of a window are in flight while its bytes are
         // converted; the scheduler must not gather several windows' reads
         // (there are no registers for them)
-        const int u = b * (kFlush / kWindow) + w;
-        dev::u32x4 bv[NT][2][NP];
+        const int u = b * (kBlock / kWindow) + w;
+        auto add_aux = [&](int mt, int e0, const float (&g)[16], int n) {
+          const float4* const wa = reinterpret_cast<const float4*>(auxt + buffer * KS + e0);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int part = 0; part < NP; ++part)
-              bv[nt][h][part] = (tb + tpos[u % 2][h])[part * kPart + 16 * nt * GPR + u / 2 * 16];
-        dev::u32x4 av[MT][2];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const int f0 = s * KS + u * kWindow + 16 * q;
-          if (XT == NB_X_FP8 && f0 + 16 > a.F) {   // NaN encodings past the last feature
-            const int nv = max(0, a.F - f0);
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const int nb = min(4, max(0, nv - 4 * d));
-              xv[mt][d] &= (nb >= 4) ? ~0u : ((1u << (8 * nb)) - 1u);
-            }
+          for (int d = 0; d < 4; ++d) {
+            if (4 * d >= n) continue;
+            const float4 w4 = wa[d];
+            aacc[mt] = fmaf(g[4 * d], w4.x, aacc[mt]);
+            aacc[mt] = fmaf(g[4 * d + 1], w4.y, aacc[mt]);
+            aacc[mt] = fmaf(g[4 * d + 2], w4.z, aacc[mt]);
+            aacc[mt] = fmaf(g[4 * d + 3], w4.w, aacc[mt]);
           }
-          float g[16];
-          to_bf16<XT, BIN>(xv[mt], av[mt][0], av[mt][1], g);
-          if constexpr (AUX) {
-            const float4* const wa = reinterpret_cast<const float4*>(auxt + buffer * KS + u * kWindow + 16 * q);
+          // summed here: left alone, the compiler moves every window's sums
+          // to the end of the unit and spills their operands
+          asm volatile("" : "+v"(aacc[mt]));
+        };
+        if constexpr (I32) {
+          // four values per lane and window, one FP32 MFMA for each
+          dev::u32x4 bv[NT];
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-              const float4 w4 = wa[d];
-              aacc[mt] = fmaf(g[4 * d], w4.x, aacc[mt]);
-              aacc[mt] = fmaf(g[4 * d + 1], w4.y, aacc[mt]);
-              aacc[mt] = fmaf(g[4 * d + 2], w4.z, aacc[mt]);
-              aacc[mt] = fmaf(g[4 * d + 3], w4.w, aacc[mt]);
+          for (int nt = 0; nt < NT; ++nt) bv[nt] = (tb + tpos4[u % 4])[16 * nt * GPR + u / 4 * 16];
+          float g[MT][16];
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              g[mt][e] = (float)(int32_t)xv[mt][e];
+              if (BIN) g[mt][e] = __builtin_amdgcn_fmed3f(g[mt][e], 0.0f, 1.0f);
             }
-            // summed here: left alone, the compiler moves every window's sums
-            // to the end of the unit and spills their operands
-            asm volatile("" : "+v"(aacc[mt]));
+            if constexpr (AUX) add_aux(mt, u * WF + 4 * q, g[mt], 4);
           }
-        }
-        if ((u + 1) % (SS / kWindow) != 0) read_window(u + 1);
+          if ((u + 1) % (SS / kWindow) != 0) read_window(u + 1);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
+          for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int part = 0; part < NP; ++part)
+              for (int mt = 0; mt < MT; ++mt)
+                acc[0][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[mt][e], __uint_as_float(bv[nt][e]),
+                                                                      acc[0][mt][nt], 0, 0, 0);
+        } else {
+          dev::u32x4 bv[NT][2][NP];
 #pragma unroll
-              for (int mt = 0; mt < MT; ++mt) {
-                f32x4& c = acc[part == 0 ? 0 : kAcc - 1][mt][nt];
-                c = mfma(av[mt][h], bv[nt][h][part], c);
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int part = 0; part < NP; ++part)
+                bv[nt][h][part] = (tb + tpos[u % 2][h])[part * kPart + 16 * nt * GPR + u / 2 * 16];
+          dev::u32x4 av[MT][2];
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            const int f0 = s * KS + u * kWindow + 16 * q;
+            if (XT == NB_X_FP8 && f0 + 16 > a.F) {   // NaN encodings past the last feature
+              const int nv = max(0, a.F - f0);
+#pragma unroll
+              for (int d = 0; d < 4; ++d) {
+                const int nb = min(4, max(0, nv - 4 * d));
+                xv[mt][d] &= (nb >= 4) ? ~0u : ((1u << (8 * nb)) - 1u);
               }
+            }
+            float g[16];
+            to_bf16<XT, BIN>(xv[mt], av[mt][0], av[mt][1], g);
+            if constexpr (AUX) add_aux(mt, u * kWindow + 16 * q, g, 16);
+          }
+          if ((u + 1) % (SS / kWindow) != 0) read_window(u + 1);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int part = 0; part < NP; ++part)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                  f32x4& c = acc[part == 0 ? 0 : kAcc - 1][mt][nt];
+                  c = mfma(av[mt][h], bv[nt][h][part], c);
+                }
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (AUX) {
@@ -397,12 +449,12 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
 
   const uint32_t voff = (uint32_t)(lr * ld) + 16u * lp;
   auto issue = [&](int64_t row0, int s, dev::u32x4 (&dst)[NL]) {
-    const int64_t base = row0 * ld + (int64_t)s * KS;
+    const int64_t base = row0 * ld + (int64_t)s * KB;
     const auto rsrc = dev::make_rsrc(a.x + base, a.total_bytes - base);
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       // bytes past the last feature belong to the next row, whose own loads fetch them
-      const bool live = s * KS + j / NLS * SS + 16 * lp < a.F;
+      const bool live = s * KB + j / NLS * SS + 16 * lp < row_bytes;
       dst[j] = dev::buffer_load16(
           rsrc, live ? voff + (uint32_t)(FPI * (j % NLS)) * (uint32_t)ld + j / NLS * SS : dev::kNoAccess);
     }
@@ -473,7 +525,7 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
       } else {
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-          const int64_t row = row0 + FPI * (j % NLS) + lr, off = row * ld + (int64_t)s * KS + j / NLS * SS + 16 * lp;
+          const int64_t row = row0 + FPI * (j % NLS) + lr, off = row * ld + (int64_t)s * KB + j / NLS * SS + 16 * lp;
           dst[j] = dev::u32x4{0u, 0u, 0u, 0u};
           if (row < a.n) dst[j] = dev::load16_guarded(a.x + off, a.total_bytes - off);
         }
@@ -503,22 +555,33 @@ using KernelFn = void (*)(ScoreTileArgs);
 
 struct TileKernel {
   KernelFn fn = nullptr;
-  int slice = 0, files = 0, units = 0, waves = 0;   // KS, 16 MT, PT, NW
+  int slice = 0, files = 0, units = 0, waves = 0;   // KB, 16 MT, PT, NW
   size_t lds = 0;
   bool aux = false;
 };
 
-template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KS, int SS, int NW, bool AUX = false>
+template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX = false>
 TileKernel tile_kernel() {
   TileKernel k;
-  k.fn = score_tile_kernel<XT, NT, NP, BIN, MT, PT, KS, SS, NW, AUX>;
-  k.slice = KS;
+  k.fn = score_tile_kernel<XT, NT, NP, BIN, MT, PT, KB, SS, NW, AUX>;
+  k.slice = KB;
   k.files = 16 * MT;
   k.units = PT;
   k.waves = NW;
-  k.lds = (size_t)2 * NP * 16 * NT * KS * 2 + (size_t)NW * 16 * MT * SS + (AUX ? 8 * KS : 0);
+  const bool i32 = XT == NB_X_I32;      // FP32 entries, KB / 4 of them
+  k.lds = (size_t)2 * (i32 ? 1 : NP) * 16 * NT * KB * (i32 ? 1 : 2) + (size_t)NW * 16 * MT * SS +
+          (AUX ? 8 * (i32 ? KB / 4 : KB) : 0);
   k.aux = AUX;
   return k;
+}
+
+// int32 features: at most 32 score rows, either table.
+template <int NP, bool BIN>
+TileKernel pick_tile_i32(int nt, bool aux) {
+  if (nt == 1 && aux) return tile_kernel<NB_X_I32, 1, NP, BIN, 1, 2, 1024, 256, 8, true>();
+  if (nt == 1) return tile_kernel<NB_X_I32, 1, NP, BIN, 1, 2, 1024, 256, 8>();
+  if (nt == 2) return tile_kernel<NB_X_I32, 2, NP, BIN, 1, 2, 1024, 256, 8>();
+  return {};
 }
 
 // The slice is as long as two slices of the table and the waves' stages fit
@@ -548,8 +611,8 @@ int round_nt(int nt) { return nt <= 4 ? nt : nt <= 8 ? 8 : nt <= 16 ? 16 : 0; }
 
 }  // namespace
 
-// Entry from nb_score for C >= 3 and byte features (arguments validated by the
-// caller).  The FP32 table takes up to 32 rows, the BF16 table up to 256.
+// Entry from nb_score for C >= 3 (arguments validated by the caller: at most 32
+// rows for the FP32 table and int32 features, 256 for byte features on BF16).
 int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int32_t xtype, int64_t n, int64_t ld,
                       int32_t wtype, int32_t* labels, float* log_post, float* scores, hipStream_t s) {
   const int C = m->n_classes;
@@ -558,15 +621,19 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   const bool aux = scores && C == 16;      // 16 classes fill the tile: the aux row would need a second one
   const int nt = aux ? 1 : round_nt((ns + 15) / 16);
   TileKernel k;
-  if (xtype == NB_X_U8) k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux) : pick_tile<NB_X_U8, false>(nt, f32, aux);
+  if (xtype == NB_X_I32) {
+    if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux) : pick_tile_i32<3, false>(nt, aux);
+    else k = bin ? pick_tile_i32<1, true>(nt, aux) : pick_tile_i32<1, false>(nt, aux);
+  } else if (xtype == NB_X_U8) k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux) : pick_tile<NB_X_U8, false>(nt, f32, aux);
   else k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux) : pick_tile<NB_X_FP8, false>(nt, f32, aux);
   if (!k.fn) return fail(NB_EINVAL, "too many score columns for the table type");
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);
   ScoreTileArgs a;
   a.x = static_cast<const uint8_t*>(x);
-  a.ld_bytes = ld;
+  const int eb = elem_bytes(xtype);
+  a.ld_bytes = ld * eb;
   a.n = n;
-  a.total_bytes = (n - 1) * ld + m->n_features;
+  a.total_bytes = ((n - 1) * ld + m->n_features) * eb;
   a.rows = base + (f32 ? L.off_form_f32 : L.off_form_bf16);
   a.row_bias = reinterpret_cast<const float*>(base + L.off_form_bias);
   a.labels = labels;
@@ -577,8 +644,8 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   a.C = C;
   a.ns = aux ? C : ns;
   // files whose slices all lie inside the buffer
-  const int64_t span = (int64_t)((a.F + k.slice - 1) / k.slice) * k.slice;
-  a.nfast = a.total_bytes >= span ? std::min(n, (a.total_bytes - span) / ld + 1) : 0;
+  const int64_t span = ((int64_t)a.F * eb + k.slice - 1) / k.slice * k.slice;
+  a.nfast = a.total_bytes >= span ? std::min(n, (a.total_bytes - span) / a.ld_bytes + 1) : 0;
   const void* fn = reinterpret_cast<const void*>(k.fn);
   NB_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds));
   const int64_t cap = (int64_t)resident_per_cu(fn, 64 * k.waves, k.lds) * device_cu_count();

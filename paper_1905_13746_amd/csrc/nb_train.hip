@@ -57,7 +57,7 @@ constexpr int64_t min_rows_per_slot(int C) { return C == 2 ? 256 : 512; }
 
 // The words that reduce_counts adds to with atomics lie on cache lines of their
 // own: 16 classes at F = 4096 send 64 additions to each of 128 words, which took
-// 23.6 us with the words side by side (additions to one line queue) and FILL_SIX
+// 23.6 us with the words side by side (additions to one line queue) and 10.5 us
 // apart.
 constexpr int kSumStride = 16;
 

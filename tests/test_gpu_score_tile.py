@@ -12,7 +12,7 @@ import torch
 import paper_1905_13746_amd as nbg
 from oracle import nb, precision as P
 from synth import workloads as W
-from tests.parity import X_FP8, X_U8, assert_scores, to_np
+from tests.parity import X_FP8, X_I32, X_U8, assert_scores, to_np
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -107,3 +107,44 @@ def test_three_parts_are_the_fp32_table(kind):
     # fl(fl(W) + bias) of the centred row, plus that of the aux row: FP32
     want = (rows[:C] + b[:C, None]) + (rows[C] + b[C])[None, :]
     assert np.array_equal(to_np(sc).T, want.astype(np.float32))
+
+
+# int32 features on FP32 MFMAs: feature counts at the edges of a lane's four, of
+# the 16-feature sums and of the 256-feature slices, and padding that is no feature
+I32 = [(3, 1, 1, 3, True), (15, 3, 17, 1, True), (16, 64, 130, 0, True), (16, 255, 129, 1, False), (16, 257, 64, 0, True),
+       (17, 512, 33, 0, True), (31, 516, 200, 4, True), (32, 1030, 65, 2, False), (7, 2049, 300, 0, True)]
+
+
+@pytest.mark.parametrize("wtype", [0, 1])
+@pytest.mark.parametrize("kind", [nb.MULTINOMIAL, nb.BERNOULLI])
+@pytest.mark.parametrize("C,F,n,pad,scores", I32, ids=[f"C{c}_F{f}_n{n}" for c, f, n, _, _ in I32])
+def test_int32_features(C, F, n, pad, scores, kind, wtype):
+    print(f"[case] int32 tile C={C} F={F} n={n} {kind} wtype={wtype}", flush=True)
+    wl = W.Workload(wid=6, n_classes=C, n_features=F, p_zero=0.7, clip255=False, group=C * 8192 + F)
+    X, y = wl.train_set(max(1000, 12 * C), device=DEV)
+    m = nbg.Model(C, F, kind)
+    nbg.train(m, X, y)
+    om = nb.train(to_np(X), to_np(y), C, kind)
+    wide = torch.full((n, F + pad), -9, dtype=torch.int32, device=DEV)
+    wide[:, :F] = wl.test_set(n, device=DEV)[0]
+    x = wide.flatten()[:(n - 1) * (F + pad) + F].as_strided((n, F), (F + pad, 1))
+    lab, lp, sc = nbg.score(m, x, wtype=wtype, scores=scores)
+    torch.cuda.synchronize()
+    assert_scores(om, to_np(x), to_np(lab), to_np(lp), to_np(sc) if scores else None, wtype=wtype, xtype=X_I32)
+
+
+def test_int32_wide_tiles_and_limits():
+    C, F, n = 16, 300, 40_003
+    wl = W.Workload(wid=6, n_classes=C, n_features=F, p_zero=0.7, clip255=False, group=5)
+    X, y = wl.train_set(1000, device=DEV)
+    m = nbg.Model(C, F, nb.MULTINOMIAL)
+    nbg.train(m, X, y)
+    T, _ = wl.test_set(n, device=DEV)
+    full = nbg.score(m, T, scores=True)
+    for a, b in ((0, 1), (100, 229), (32_767, 32_800), (n - 150, n)):
+        for u, v in zip(full, nbg.score(m, T[a:b], scores=True)):
+            assert torch.equal(u[a:b], v)
+    for wtype in (nbg.W_F32, nbg.W_BF16):        # 33 score rows stay refused
+        with pytest.raises(nbg.NBError) as e:
+            nbg.score(nbg.Model(32, 8, nb.MULTINOMIAL), T[:10, :8].contiguous(), wtype=wtype, scores=True)
+        assert e.value.code == -1
