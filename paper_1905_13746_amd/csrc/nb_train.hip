@@ -31,6 +31,10 @@
 //                 tree reduction (deterministic).
 //   form_rows     the scoring rows (log-odds / class-centred + aux) in FP64,
 //                 rounded once to FP32 and to BF16.
+//   tables_rows2, tables_rowsC   both in one launch, for multinomial models on
+//                 byte features (two classes, more).
+//   gauss_tables2 everything behind reduce_counts for a Gaussian model of two
+//                 classes.
 #include <algorithm>
 #include <cmath>
 
@@ -962,6 +966,7 @@ __global__ __launch_bounds__(256) void gauss_rows(const double* __restrict__ mea
 // Threads 256 c .. 256 c + 255 are class c's workgroup of those kernels: the
 // same expressions and the same order of every sum.  14 us at F = 1000, where
 // the five took 26 us and the gaps between them.
+constexpr int kGaussTables2 = 8192;   // the widest model that is scored; one workgroup's loops grow with F
 __global__ __launch_bounds__(512) void gauss_tables2(TableArgs a, const int64_t* __restrict__ part2_sq, int64_t* sumsq,
                                                      double* __restrict__ mean, double* __restrict__ var,
                                                      double* __restrict__ eps_out, float* __restrict__ mu32,
@@ -1135,6 +1140,8 @@ int count_capacity(int32_t xtype, int win, bool sq) {
 constexpr int64_t kManyClassRounds = 4;
 struct Slots {
   int64_t rows, n;       // rows per slot, slots
+  int64_t most;          // slots the workspace holds: never fewer for more rows, so that
+                         // a workspace for n files serves every smaller call
 };
 Slots train_slots(int32_t C, int32_t F, int64_t n, int32_t xtype, bool sq = false) {
   const int64_t nch = (align_up((size_t)F, kFeaturePad)) / kChunk;
@@ -1144,8 +1151,8 @@ Slots train_slots(int32_t C, int32_t F, int64_t n, int32_t xtype, bool sq = fals
   const int64_t by_rows = std::max<int64_t>(1, (n + min_rows_per_slot(C) - 1) / min_rows_per_slot(C));
   const int64_t list = (int64_t)kWaves * 64 * count_win(C);
   Slots t;
-  t.n = std::max<int64_t>(1, std::min(s, by_rows));
-  t.rows = std::max<int64_t>(1, (n + t.n - 1) / t.n);
+  t.most = std::max<int64_t>(1, std::min(s, by_rows));
+  t.rows = std::max<int64_t>(1, (n + t.most - 1) / t.most);
   if (C > 2 && t.rows > list) t.rows = (t.rows + list - 1) / list * list;
   t.n = std::max<int64_t>(1, (n + t.rows - 1) / t.rows);
   return t;
@@ -1390,7 +1397,7 @@ int launch_tables(nb_model* m, const nb_layout& L, const int64_t* part2, const i
     NB_HIP_CHECK(hipGetLastError());
     return NB_OK;
   }
-  if (m->kind == NB_GAUSSIAN && ta.C == 2) {
+  if (m->kind == NB_GAUSSIAN && ta.C == 2 && ta.F <= kGaussTables2) {
     hipLaunchKernelGGL(gauss_tables2, dim3(1), dim3(512), 0, s, ta, part2_sq,
                        reinterpret_cast<int64_t*>(base + L.off_sumsq), reinterpret_cast<double*>(base + L.off_mean),
                        reinterpret_cast<double*>(base + L.off_var), reinterpret_cast<double*>(base + L.off_epsilon),
@@ -1459,7 +1466,7 @@ extern "C" {
 size_t nb_train_workspace_bytes(int32_t n_classes, int32_t n_features, int64_t n, int32_t xtype) {
   nb_layout L;
   if (!compute_layout(n_classes, n_features, &L) || n < 0 || elem_bytes(xtype) == 0) return 0;
-  return train_ws(n_classes, L.padded_features, train_slots(n_classes, n_features, n, xtype).n).total;
+  return train_ws(n_classes, L.padded_features, train_slots(n_classes, n_features, n, xtype).most).total;
 }
 
 int nb_train(nb_model* m, const void* x, int32_t xtype, int64_t n, int64_t ld, const int32_t* y,
