@@ -18,7 +18,7 @@ step's inputs.  Extra objects (skip with --no-extras):
   f_sweep    scoring bandwidth of the two-class kernel at F = 100, 500, 5000, of
              the Bernoulli form at F = 1000 (with its training time), and of the
              int32-feature variant at F = 1000
-  precision  16 classes, F = 4096, 4,000,000 files: the plain FP32 vector path
+  precision  16 classes, F = 4096, 4,000,000 files: the plain FP32 path
              vs the BF16 table on the matrix cores (uint8 and FP8 features),
              with the labels of the paths compared on every file.
   groups     256 size groups with lognormal(7, 1.5) file counts in [100, 1e5],
@@ -305,7 +305,7 @@ def f_sweep(nbg, W):
 
 
 def precision_compare(nbg, W, fill: bool = False):
-    """16 classes, F = 4096, 4M files: FP32 table on the vector ALUs vs the
+    """16 classes, F = 4096, 4M files: FP32 table (three BF16 parts) vs the
     BF16 table on the matrix cores, uint8 and FP8-e4m3 features, with the
     labels of the paths compared on every file.  Agreement with the FP64
     oracle (inside the certified band) is the business of the parity tests

@@ -129,7 +129,8 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
   constexpr int kAcc = NPS == 3 ? 2 : 1;     // accumulators: leading parts, lower parts
   constexpr int TG = (kPart + kThreads - 1) / kThreads;   // table granules staged per thread
   constexpr bool kWhole = kPart % kThreads == 0;           // else the last ones are absent
-  extern __shared__ __attribute__((aligned(16))) dev::u32x4 lds4[];   // [2][NPS][16 NT][GPR], the stages, AUX: [2][KS] floats
+  // [2][NPS][16 NT][GPR], the stages, AUX: [2][KS] floats
+  extern __shared__ __attribute__((aligned(16))) dev::u32x4 lds4[];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -440,7 +441,8 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
           const int c = 16 * nt + col;
           const uint32_t off = c < a.C ? (uint32_t)(r * a.C + c) * 4u : dev::kNoAccess;
           __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sv[nt] - lse), rp, (int)off, 0, 0);
-          if (AUX || a.ns > a.C) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sv[nt] + aux), rs, (int)off, 0, 0);
+          if (AUX || a.ns > a.C)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sv[nt] + aux), rs, (int)off, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -624,8 +626,11 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   if (xtype == NB_X_I32) {
     if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux) : pick_tile_i32<3, false>(nt, aux);
     else k = bin ? pick_tile_i32<1, true>(nt, aux) : pick_tile_i32<1, false>(nt, aux);
-  } else if (xtype == NB_X_U8) k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux) : pick_tile<NB_X_U8, false>(nt, f32, aux);
-  else k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux) : pick_tile<NB_X_FP8, false>(nt, f32, aux);
+  } else if (xtype == NB_X_U8) {
+    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux) : pick_tile<NB_X_U8, false>(nt, f32, aux);
+  } else {
+    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux) : pick_tile<NB_X_FP8, false>(nt, f32, aux);
+  }
   if (!k.fn) return fail(NB_EINVAL, "too many score columns for the table type");
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);
   ScoreTileArgs a;
