@@ -32,7 +32,7 @@
 // the FP32 table, int32 features and fewer than 16 classes, a matrix-core kernel
 // on 64-byte loads for the rest):
 //   FP32, 16 classes, F = 4096, 400,003 files        1,718 ->  354  (4.6 TB/s)
-//   the same with raw scores                         1,980 ->  378
+//   the same with raw scores                         1,980 ->  363
 //   FP32, 20 classes, F = 2000, 300,000 files          905 ->  204
 //   FP32, 7 classes, F = 1000, 600,000 files           347 ->  152
 //   FP32, 16 classes, F = 1000, 2,000 files            128 ->   13
@@ -589,11 +589,14 @@ TileKernel pick_tile_i32(int nt, bool aux) {
 // The slice is as long as two slices of the table and the waves' stages fit
 // the 160 KB of LDS.
 template <int XT, bool BIN>
-TileKernel pick_tile(int nt, bool f32, bool aux) {
+TileKernel pick_tile(int nt, bool f32, bool aux, bool four) {
   if (f32) {
-    if (nt == 1 && aux) return tile_kernel<XT, 1, 3, BIN, 1, 2, 512, 128, 8, true>();
+    if (nt == 1 && aux)
+      return four ? tile_kernel<XT, 1, 3, BIN, 1, 4, 512, 128, 8, true>()
+                  : tile_kernel<XT, 1, 3, BIN, 1, 2, 512, 128, 8, true>();
     if (nt == 1) return tile_kernel<XT, 1, 3, BIN, 1, 2, 512, 256, 8>();
-    if (nt == 2) return tile_kernel<XT, 2, 3, BIN, 1, 4, 256, 256, 8>();
+    if (nt == 2)
+      return four ? tile_kernel<XT, 2, 3, BIN, 1, 4, 256, 256, 8>() : tile_kernel<XT, 2, 3, BIN, 1, 2, 256, 256, 8>();
     return {};
   }
   if (nt == 1 && aux) return tile_kernel<XT, 1, 1, BIN, 1, 2, 512, 512, 4, true>();
@@ -622,14 +625,21 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   const bool f32 = wtype == NB_W_F32, bin = m->kind == NB_BERNOULLI;
   const bool aux = scores && C == 16;      // 16 classes fill the tile: the aux row would need a second one
   const int nt = aux ? 1 : round_nt((ns + 15) / 16);
+  // Four units per wave and slice where the FP32 table does not stay in LDS and
+  // every workgroup gets four (its slices are then staged half as often: 16
+  // classes, raw scores, F = 4096, 400,003 files 379 us with two, 362 with four);
+  // two otherwise (90,000 files: 100 us, where four leave only single-unit tiles,
+  // 116; a resident table, F = 700: 189 against 193).  Sums are the same.
+  const int64_t per_round = (int64_t)128 * device_cu_count();
+  const bool four = f32 && m->n_features > 1024 && n >= 4 * per_round;
   TileKernel k;
   if (xtype == NB_X_I32) {
     if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux) : pick_tile_i32<3, false>(nt, aux);
     else k = bin ? pick_tile_i32<1, true>(nt, aux) : pick_tile_i32<1, false>(nt, aux);
   } else if (xtype == NB_X_U8) {
-    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux) : pick_tile<NB_X_U8, false>(nt, f32, aux);
+    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four) : pick_tile<NB_X_U8, false>(nt, f32, aux, four);
   } else {
-    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux) : pick_tile<NB_X_FP8, false>(nt, f32, aux);
+    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four);
   }
   if (!k.fn) return fail(NB_EINVAL, "too many score columns for the table type");
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);

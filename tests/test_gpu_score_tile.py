@@ -80,6 +80,19 @@ def test_wide_tiles_equal_small_calls(C, F, n, wtype):
     assert none is None and torch.equal(lab, full[0])
 
 
+@pytest.mark.parametrize("C,F,n", [(16, 1028, 131_072 + 301), (20, 1540, 140_001)])
+def test_four_units_per_slice_equal_small_calls(C, F, n):
+    """FP32 tables that do not stay in LDS, enough files for four units per wave."""
+    print(f"[case] four units C={C} F={F} n={n}", flush=True)
+    wl, m, _ = _model(C, F, nb.MULTINOMIAL)
+    base, _ = wl.test_set(1999, device=DEV)
+    X = base.repeat(n // 1999 + 1, 1)[:n]
+    want = nbg.score(m, base, scores=True)
+    rows = torch.arange(n, device=DEV) % 1999
+    for u, v in zip(nbg.score(m, X, scores=True), want):
+        assert torch.equal(u, v[rows])
+
+
 def test_fp8_values_past_the_last_feature():
     """NaN encodings in the padding bytes are not features."""
     C, F = 20, 500
