@@ -45,7 +45,11 @@
 // Sums: the products of 128 consecutive features (16 int32 ones) go to fresh
 // accumulators (leading parts and lower parts apart), whose sum is added to the
 // file's running totals: a term passes through few roundings, and the order depends on
-// the feature index alone.
+// the feature index alone.  Sixteen classes on the BF16 table are the exception
+// (ROW): where the kernel of nb_score_mfma.hip takes the calls without raw scores,
+// the ones with them sum as it does, in one accumulator per row and with its order of
+// the log-sum-exp, so that what is asked for beside them changes no label and no log
+// posterior.
 #include <algorithm>
 #include <type_traits>
 
@@ -92,6 +96,17 @@ __device__ __forceinline__ int ror16(int v) {
   return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, true);
 }
 
+// The four lanes' sum, then eight's, then sixteen's: the order of a butterfly over
+// lane distances 1, 2, 4 and 8 (equal within the lanes already summed, so mirrored
+// lanes stand for the exchanged ones).
+__device__ __forceinline__ float butterfly16(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));    // lanes 1 0 3 2
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));    // lanes 2 3 0 1
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));   // half row mirror
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true));   // row mirror
+  return v;
+}
+
 template <int N>
 __device__ __forceinline__ void argmax_step(float& m, int& best) {
   const float om = ror16<N>(m);
@@ -107,13 +122,15 @@ __device__ __forceinline__ void argmax_step(float& m, int& best) {
 // the two load buffers alternate).  KB: bytes per file of a slice.  SS: bytes per
 // file of the stage.  NW: waves.  AUX: the raw scores' aux row, which would need a column
 // tile of its own, is contracted on the vector ALUs (one FMA per byte, a
-// quarter of a lane's operations) from the FP32 values at hand.
-template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX>
+// quarter of a lane's operations) from the FP32 values at hand.  ROW: one
+// accumulator per row.
+template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX, bool ROW>
 __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
   constexpr bool I32 = XT == NB_X_I32;
   constexpr int EB = I32 ? 4 : 1;           // bytes per feature
   constexpr int KS = KB / EB;               // features per slice
   constexpr int WF = kWindow / EB;          // features per window
+  static_assert(!ROW || (NP == 1 && !I32), "one accumulator");
   static_assert(PT % 2 == 0 && SS % kFlush == 0 && KB % SS == 0 && 1024 % KB == 0, "tile shape");
   constexpr int kThreads = 64 * NW;
   constexpr int GF = 16 * MT;               // files per unit
@@ -282,6 +299,12 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
       f32x4 acc[kAcc][MT][NT];
 #pragma unroll
       for (int h = 0; h < kAcc; ++h) zero(acc[h]);
+      if constexpr (ROW) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[0][mt][nt] = tot[mt][nt];
+      }
       float aacc[MT] = {};
 #pragma unroll
       for (int w = 0; w < kBlock / kWindow; ++w) {
@@ -375,8 +398,10 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          tot[mt][nt] += kAcc == 2 ? acc[0][mt][nt] + acc[kAcc - 1][mt][nt] : acc[0][mt][nt];
+        for (int nt = 0; nt < NT; ++nt) {
+          if constexpr (ROW) tot[mt][nt] = acc[0][mt][nt];
+          else tot[mt][nt] += kAcc == 2 ? acc[0][mt][nt] + acc[kAcc - 1][mt][nt] : acc[0][mt][nt];
+        }
     }
   };
 
@@ -420,10 +445,14 @@ __global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
         float z = 0.0f;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) z += (16 * nt + col < a.C) ? __expf(sv[nt] - m) : 0.0f;
-        z += ror16<8>(z);
-        z += ror16<4>(z);
-        z += ror16<2>(z);
-        z += ror16<1>(z);
+        if constexpr (ROW) {
+          z = butterfly16(z);
+        } else {
+          z += ror16<8>(z);
+          z += ror16<4>(z);
+          z += ror16<2>(z);
+          z += ror16<1>(z);
+        }
         const float lse = m + __logf(z);
         best = best < a.C ? best : 0;      // no sum compares (NaN features)
         __builtin_amdgcn_raw_buffer_store_b32((uint32_t)best, rl, (int)(col == 0 ? 4u * r : dev::kNoAccess), 0, 0);
@@ -562,10 +591,10 @@ struct TileKernel {
   bool aux = false;
 };
 
-template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX = false>
+template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX = false, bool ROW = false>
 TileKernel tile_kernel() {
   TileKernel k;
-  k.fn = score_tile_kernel<XT, NT, NP, BIN, MT, PT, KB, SS, NW, AUX>;
+  k.fn = score_tile_kernel<XT, NT, NP, BIN, MT, PT, KB, SS, NW, AUX, ROW>;
   k.slice = KB;
   k.files = 16 * MT;
   k.units = PT;
@@ -589,7 +618,7 @@ TileKernel pick_tile_i32(int nt, bool aux) {
 // The slice is as long as two slices of the table and the waves' stages fit
 // the 160 KB of LDS.
 template <int XT, bool BIN>
-TileKernel pick_tile(int nt, bool f32, bool aux, bool four) {
+TileKernel pick_tile(int nt, bool f32, bool aux, bool four, bool row) {
   if (f32) {
     if (nt == 1 && aux)
       return four ? tile_kernel<XT, 1, 3, BIN, 1, 4, 512, 128, 8, true>()
@@ -599,7 +628,9 @@ TileKernel pick_tile(int nt, bool f32, bool aux, bool four) {
       return four ? tile_kernel<XT, 2, 3, BIN, 1, 4, 256, 256, 8>() : tile_kernel<XT, 2, 3, BIN, 1, 2, 256, 256, 8>();
     return {};
   }
-  if (nt == 1 && aux) return tile_kernel<XT, 1, 1, BIN, 1, 2, 512, 512, 4, true>();
+  if (nt == 1 && aux)
+    return row ? tile_kernel<XT, 1, 1, BIN, 1, 2, 512, 512, 4, true, true>()
+               : tile_kernel<XT, 1, 1, BIN, 1, 2, 512, 512, 4, true>();
   switch (nt) {
     case 1: return tile_kernel<XT, 1, 1, BIN, 1, 2, 512, 256, 4>();
     case 2: return tile_kernel<XT, 2, 1, BIN, 1, 2, 512, 512, 8>();
@@ -632,14 +663,15 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   // 116; a resident table, F = 700: 189 against 193).  Sums are the same.
   const int64_t per_round = (int64_t)128 * device_cu_count();
   const bool four = f32 && m->n_features > 1024 && n >= 4 * per_round;
+  const bool row = xtype != NB_X_I32 && score16_staged(m, L, wtype, nullptr);
   TileKernel k;
   if (xtype == NB_X_I32) {
     if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux) : pick_tile_i32<3, false>(nt, aux);
     else k = bin ? pick_tile_i32<1, true>(nt, aux) : pick_tile_i32<1, false>(nt, aux);
   } else if (xtype == NB_X_U8) {
-    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four) : pick_tile<NB_X_U8, false>(nt, f32, aux, four);
+    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four, row) : pick_tile<NB_X_U8, false>(nt, f32, aux, four, row);
   } else {
-    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four);
+    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four, row) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four, row);
   }
   if (!k.fn) return fail(NB_EINVAL, "too many score columns for the table type");
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);

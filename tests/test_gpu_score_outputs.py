@@ -1,0 +1,32 @@
+"""What a call asks for changes nothing of what it returns: the order of a file's
+sums depends on the features, classes, feature type and table type alone, so labels
+and log posteriors are the same bits with and without raw scores, in whatever kernel
+a call runs (16 classes on the BF16 table have one of their own without raw scores,
+up to 4,096 features)."""
+import pytest
+import torch
+
+import paper_1905_13746_amd as nbg
+from synth import workloads as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("kind", ["multinomial", "bernoulli"])
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("C,F", [(15, 600), (16, 60), (16, 1000), (16, 4096), (16, 4100), (17, 600), (32, 300)])
+def test_raw_scores_change_no_other_output(C, F, fp8, kind):
+    print(f"[case] outputs C={C} F={F} fp8={fp8} {kind}", flush=True)
+    wl = W.Workload(wid=6, n_classes=C, n_features=F, p_zero=0.6, clip255=True, group=C * 8192 + F)
+    X, y = wl.train_set(12 * C, device=DEV)
+    m = nbg.Model(C, F, kind)
+    nbg.train(m, X, y)
+    T, _ = wl.test_set(6007, device=DEV)
+    T[:, : F // 2] *= 7          # sums that round
+    x = W.to_fp8_e4m3(T) if fp8 else T
+    for n in (1, 37, 6007):
+        lab, lp, _ = nbg.score(m, x[:n], wtype=nbg.W_BF16, fp8=fp8)
+        lab2, lp2, sc = nbg.score(m, x[:n], wtype=nbg.W_BF16, fp8=fp8, scores=True)
+        assert torch.equal(lab, lab2) and torch.equal(lp, lp2), n
+        assert torch.isfinite(sc).all()
