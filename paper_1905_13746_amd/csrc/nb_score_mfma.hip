@@ -18,6 +18,7 @@
 // lanes of each column group for the max / log-sum-exp epilogue; labels take
 // the lowest class index among maxima.
 #include <algorithm>
+#include <type_traits>
 
 #include "nb_internal.hpp"
 #include "nb_mfma.hpp"
@@ -32,78 +33,13 @@ struct ScoreMArgs {
   int64_t ld_bytes;
   int64_t n;
   int64_t total_bytes;
-  const uint16_t* rows16;   // [P+1][Fp] class-major BF16 rows (centred rows, aux row C)
-  const float* row_bias;    // [P+1]
+  const uint16_t* rows16;   // [16][Fp] class-major BF16 rows
+  const float* row_bias;    // [16]
   int32_t* labels;
   float* log_post;
-  float* scores;
-  int32_t F, Fp, C, ns;     // ns: rows used (C, or C + 1 with the aux row)
-  int64_t nfast;            // staged kernel: leading wave tiles with every row and load in bounds
+  int32_t F, Fp;
+  int64_t nfast;            // leading wave tiles with every row and load in bounds
 };
-
-// Epilogue of a 16*MT-file tile: lane holds files 4q + i (i < 4) of each M
-// tile for class 16 nt + col.  Max and lowest arg-max over the 16 lanes of a
-// column group, log-sum-exp, then labels, log posteriors and raw scores.
-template <int NT, int MT>
-__device__ __forceinline__ void epilogue(const ScoreMArgs& a, f32x4 (&acc)[MT][NT], int lane, int64_t row0) {
-  const int col = lane & 15, q = lane >> 4;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t row = row0 + 16 * mt + 4 * q + i;
-      float s[NT];
-      float m = -INFINITY;
-      int best = 1 << 30;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const int c = 16 * nt + col;
-        s[nt] = acc[mt][nt][i] + ((c < a.ns) ? a.row_bias[c] : 0.0f);
-        if (c < a.C && s[nt] > m) {
-          m = s[nt];
-          best = c;
-        }
-      }
-      // max and lowest arg-max over the 16 lanes of this column group
-#pragma unroll
-      for (int sh = 1; sh < 16; sh <<= 1) {
-        const float om = __shfl_xor(m, sh);
-        const int ob = __shfl_xor(best, sh);
-        if (om > m || (om == m && ob < best)) {
-          m = om;
-          best = ob;
-        }
-      }
-      float z = 0.0f;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        if (16 * nt + col < a.C) z += __expf(s[nt] - m);
-#pragma unroll
-      for (int sh = 1; sh < 16; sh <<= 1) z += __shfl_xor(z, sh);
-      const float lse = m + __logf(z);
-      // aux row (raw-score offset) lives in column C
-      float aux = 0.0f;
-      if (a.ns > a.C) {
-        float mine = 0.0f;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          if (16 * nt + col == a.C) mine = s[nt];
-        aux = __shfl(mine, (lane & ~15) | (a.C & 15));
-      }
-      if (row < a.n) {
-        if (a.labels && col == 0) a.labels[row] = best;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const int c = 16 * nt + col;
-          if (c < a.C) {
-            if (a.log_post) a.log_post[row * a.C + c] = s[nt] - lse;
-            if (a.scores) a.scores[row * a.C + c] = s[nt] + aux;
-          }
-        }
-      }
-    }
-  }
-}
 
 // One column tile (16 score rows) and Fp <= 4096.  A wave tile is 16 files; a group is 512 features.  Each group's loads
 // read 512 contiguous bytes of each of the 16 files (a wave instruction
@@ -133,8 +69,8 @@ constexpr int kStageLoads = kStageFiles / kStageFPI;   // 16-byte loads per lane
 constexpr int kStageBytes = kStageFiles * kStageGB;
 static_assert(kStageGB >= 128 && kStageGB <= 1024 && kStageFiles % kStageFPI == 0, "stage shape");
 constexpr int kStageDepth = 3;
-// Destination of outputs the caller did not request (and of the lanes that
-// hold no label): the fast path stores unconditionally so that the number of
+// Destination of outputs the caller did not request, of the lanes that hold no
+// label and of absent rows: the epilogue stores unconditionally so that the number of
 // memory operations in flight stays known at compile time.
 __device__ int32_t g_stage_sink_label[64];
 __device__ float g_stage_sink_post[64 * 16];
@@ -144,12 +80,9 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
   extern __shared__ __attribute__((aligned(16))) dev::u32x4 lds4[];
   dev::u32x4* tbl = lds4;                                    // [16][Fp / 8] granules, swizzled
   const int gpr = a.Fp / 8;                                  // granules per table row
-  // stage the table (rows >= ns are zero)
   for (int i = threadIdx.x; i < 16 * gpr; i += kStageThreads) {
     const int r = i / gpr, g = i - r * gpr;
-    dev::u32x4 v = {0u, 0u, 0u, 0u};
-    if (r < a.ns) v = *reinterpret_cast<const dev::u32x4*>(a.rows16 + (int64_t)r * a.Fp + 8 * g);
-    tbl[r * gpr + (g ^ r)] = v;
+    tbl[r * gpr + (g ^ r)] = *reinterpret_cast<const dev::u32x4*>(a.rows16 + (int64_t)r * a.Fp + 8 * g);
   }
   __syncthreads();
 
@@ -161,7 +94,7 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
   const int64_t wave_id = (int64_t)blockIdx.x * kStageWaves + wave;
   const int64_t nwaves = (int64_t)gridDim.x * kStageWaves;
   const int ngroups = (a.F + kStageGB - 1) / kStageGB;
-  const float bias = (col < a.ns) ? a.row_bias[col] : 0.0f;
+  const float bias = a.row_bias[col];
   // load lane layout: instruction j covers files kStageFPI j + lane / kStageNG,
   // granule lane % kStageNG
   const int lr = lane / kStageNG, lp = lane % kStageNG;
@@ -220,10 +153,14 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
       }
     }
   };
-  // Fast epilogue: 16 classes in the 16 columns, every row present, every
-  // store issued (to a sink when the output was not requested).
+  // Epilogue of a tile, 16 classes in the 16 columns (lane: files 4 q + i of
+  // class col): max and lowest arg-max over the 16 lanes of a file, log-sum-exp.
+  // A file whose sums are all NaN (an FP8 NaN among its features) compares with
+  // nothing and keeps label 0.  FULL: every row is present and every store is
+  // issued (to a sink when the output was not requested).
   const bool want_lab = a.labels != nullptr, want_lp = a.log_post != nullptr;
-  auto finish_fast = [&](int64_t row0) {
+  auto finish = [&](int64_t row0, auto full) {
+    constexpr bool FULL = decltype(full)::value;
 #pragma unroll
     for (int mt = 0; mt < kStageMT; ++mt) {
 #pragma unroll
@@ -245,8 +182,9 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
 #pragma unroll
         for (int sh = 1; sh < 16; sh <<= 1) z += __shfl_xor(z, sh);
         const float lse = m + __logf(z);
-        int32_t* pl = (want_lab && col == 0) ? a.labels + row : g_stage_sink_label + lane;
-        float* pp = want_lp ? a.log_post + row * 16 + col : g_stage_sink_post + lane;
+        const bool present = FULL || row < a.n;
+        int32_t* pl = (want_lab && present && col == 0) ? a.labels + row : g_stage_sink_label + lane;
+        float* pp = (want_lp && present) ? a.log_post + row * 16 + col : g_stage_sink_post + lane;
         *pl = best;
         *pp = sv - lse;
       }
@@ -271,7 +209,7 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
   auto consume = [&](const dev::u32x4 (&src)[kStageLoads]) {
     compute_group(cg, src);
     if (++cg == ngroups) {
-      finish_fast((wave_id + (int64_t)ct * nwaves) * kStageFiles);
+      finish((wave_id + (int64_t)ct * nwaves) * kStageFiles, std::true_type{});
       zero_acc();
       cg = 0;
       ++ct;
@@ -297,7 +235,7 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
     }
   }
 
-  // ---- remaining tiles: guarded loads, partial rows, generic epilogue
+  // ---- remaining tiles: guarded loads, partial rows
   const int64_t nwtile = (a.n + kStageFiles - 1) / kStageFiles;
   for (int64_t wt = a.nfast + wave_id; wt < nwtile; wt += nwaves) {
     const int64_t row0 = wt * kStageFiles;
@@ -313,7 +251,7 @@ __global__ __launch_bounds__(kStageThreads) void scoreM_stage_kernel(ScoreMArgs 
       }
       compute_group(g, v);
     }
-    epilogue<1, kStageMT>(a, acc, lane, row0);
+    finish(row0, std::false_type{});
   }
 }
 
@@ -352,11 +290,8 @@ int launch_score16_staged(const nb_model* m, const nb_layout& L, const void* x, 
   a.row_bias = reinterpret_cast<const float*>(base + L.off_form_bias);
   a.labels = labels;
   a.log_post = log_post;
-  a.scores = nullptr;
   a.F = m->n_features;
   a.Fp = L.padded_features;
-  a.C = m->n_classes;
-  a.ns = m->n_classes;
   // leading tiles whose rows all exist and whose group loads stay in the buffer
   const int64_t span = (int64_t)((a.F + kStageGB - 1) / kStageGB) * kStageGB;
   const int64_t full = n / kStageFiles;

@@ -30,3 +30,25 @@ def test_raw_scores_change_no_other_output(C, F, fp8, kind):
         lab2, lp2, sc = nbg.score(m, x[:n], wtype=nbg.W_BF16, fp8=fp8, scores=True)
         assert torch.equal(lab, lab2) and torch.equal(lp, lp2), n
         assert torch.isfinite(sc).all()
+
+
+@pytest.mark.parametrize("C,wtype,scores", [(16, nbg.W_BF16, False), (16, nbg.W_BF16, True), (16, nbg.W_F32, False),
+                                            (20, nbg.W_BF16, False)])
+def test_nan_features(C, wtype, scores):
+    """A file with an FP8 NaN among its features has NaN log posteriors and label 0,
+    wherever it lies (the last 16 files run with guarded loads), and the files
+    beside it are what they are without it."""
+    F, n = 500, 75
+    wl = W.Workload(wid=6, n_classes=C, n_features=F, p_zero=0.6, clip255=True, group=C)
+    X, y = wl.train_set(12 * C, device=DEV)
+    m = nbg.Model(C, F, "multinomial")
+    nbg.train(m, X, y)
+    x = W.to_fp8_e4m3(wl.test_set(n, device=DEV)[0])
+    want = nbg.score(m, x, wtype=wtype, fp8=True, scores=scores)
+    bad = torch.tensor([0, 5, 33, 64, 73, 74], device=DEV)
+    x[bad, torch.arange(len(bad), device=DEV) * 99] = 0x7F
+    lab, lp, _ = nbg.score(m, x, wtype=wtype, fp8=True, scores=scores)
+    good = torch.ones(n, dtype=torch.bool, device=DEV)
+    good[bad] = False
+    assert torch.isnan(lp[bad]).all() and (lab[bad] == 0).all()
+    assert torch.equal(lp[good], want[1][good]) and torch.equal(lab[good], want[0][good])
