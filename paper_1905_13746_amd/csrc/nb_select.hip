@@ -468,6 +468,21 @@ const void* pick_gather(int nl, int rw, int q) {
   }
 }
 
+// Workgroups per CU of a gather whose waves have `bytes` in flight each: as many
+// as put `kb` KB in flight, at least two.  More of them lie further apart in memory
+// or push each other's lines out of the caches; fewer leave the memory idle.
+// Staged rows, 100 KB, outputs counted twice (500,001 or 500,000 files, two
+// workgroups against as many as fit): bytes, F = 2000, k = 200: 203.4 and 213.7 us
+// (three: 213.2); F = 500, k = 50: 63 and 69; F = 64, k = 4: 46 and 36; F = 400, k =
+// 4: 50 and 47.  Rows gathered from memory (50,000 int32 files, F = 4000; two
+// workgroups against eight): 160 KB of cache lines, k = 20: 47 and 19, k = 50: 86
+// and 46, k = 200: 138 and 146; where a line is read again (more than twice 128
+// bytes per output in a row) 64 KB, as it has to stay: bytes, F = 4000, k = 200: 46
+// and 55.
+int64_t gather_workgroups(int resident, int64_t kb, int64_t bytes) {
+  return std::min<int64_t>(resident, std::max<int64_t>(2, kb * 1024 / (kGatherWaves * std::max<int64_t>(1, bytes))));
+}
+
 // Span of unit u (rows u*rw ..) from its 16-byte boundary, rounded up to
 // whole 16-byte loads: end offset relative to x.
 int64_t unit_end(int64_t u, int64_t rw, int64_t n, int64_t ld_bytes, int64_t row_bytes) {
@@ -564,7 +579,7 @@ int nb_gather_features(const void* x, int32_t xtype, int64_t n, int32_t F, int64
     nl = (a.row_bytes + 15 <= kGatherUnitKB * 1024) ? kGatherUnitKB : 8;
   const void* fn;
   size_t lds = 0;
-  int64_t rw = 1;
+  int64_t rw = 1, per_cu;
   if (nl) {
     const int64_t pad = a.ld_bytes - a.row_bytes;
     if (nl == kGatherUnitKB && pad * 8 <= a.ld_bytes) {
@@ -576,11 +591,15 @@ int nb_gather_features(const void* x, int32_t xtype, int64_t n, int32_t F, int64
         }
     }
     lds = (size_t)kGatherWaves * nl * 1024;
-    // no fewer units than resident waves
-    const void* f1 = (es == 1) ? pick_gather<1>(nl, (int)rw, q) : pick_gather<4>(nl, (int)rw, q);
-    const int64_t waves = (int64_t)resident_per_cu(f1, kGatherThreads, lds) * device_cu_count() * kGatherWaves;
-    while (rw > 1 && (n + rw - 1) / rw < waves) rw /= 2;
-    fn = (es == 1) ? pick_gather<1>(nl, (int)rw, q) : pick_gather<4>(nl, (int)rw, q);
+    auto pick = [&]() { return (es == 1) ? pick_gather<1>(nl, (int)rw, q) : pick_gather<4>(nl, (int)rw, q); };
+    auto launched = [&]() {
+      return gather_workgroups(resident_per_cu(pick(), kGatherThreads, lds), 100,
+                               2 * rw * (a.ld_bytes + 2 * (int64_t)k * es));
+    };
+    // no fewer units than waves launched for them
+    while (rw > 1 && (n + rw - 1) / rw < launched() * device_cu_count() * kGatherWaves) rw /= 2;
+    fn = pick();
+    per_cu = launched();
     // units whose whole rounded span lies inside the buffer (all but the last few)
     const int64_t nunits = (n + rw - 1) / rw;
     int64_t nf = nunits;
@@ -590,11 +609,11 @@ int nb_gather_features(const void* x, int32_t xtype, int64_t n, int32_t F, int64
   } else {
     fn = (es == 1) ? reinterpret_cast<const void*>(gather_global_kernel<1>)
                    : reinterpret_cast<const void*>(gather_global_kernel<4>);
+    const int64_t step = std::min(k, 256);     // outputs of a wave at once, and the cache lines these touch
+    const int64_t lines = std::min(step * 128, (int64_t)a.row_bytes * step / k);
+    per_cu = gather_workgroups(resident_per_cu(fn, kGatherThreads, 0), step * 128 < 2 * lines ? 160 : 64, lines);
   }
-  // two workgroups per CU: with as many as fit, the units in flight lie further
-  // apart in memory (500,001 byte files, F = 2000, k = 200: 213.7 us; 203.4 with
-  // two, 213.2 with three; int32, F = 1000, k = 100: 121.4 and 119.6 with two)
-  const int64_t cap_wg = (int64_t)std::min(2, resident_per_cu(fn, kGatherThreads, lds)) * device_cu_count();
+  const int64_t cap_wg = per_cu * device_cu_count();
   const int64_t units = (n + rw - 1) / rw;
   const int64_t need = (units + kGatherWaves - 1) / kGatherWaves;
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min(need, cap_wg));

@@ -1,0 +1,41 @@
+"""Launch rules that leave a shape waiting on memory: a call's time against the time
+of reading as many bytes as it has to touch (the read probe), taken as the best of
+several batches in turn.  The factors lie between what a rule that fills the device
+takes and what one measured that does not."""
+import pytest
+import torch
+
+import paper_1905_13746_amd as nbg
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _us(*calls, batches=7, reps=20):
+    """Best time per call of each, in microseconds."""
+    best = [float("inf")] * len(calls)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for batch in range(batches + 1):
+        for i, call in enumerate(calls):
+            a.record()
+            for _ in range(reps):
+                call()
+            b.record()
+            b.synchronize()
+            if batch:
+                best[i] = min(best[i], a.elapsed_time(b) / reps * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("dtype,F,ld,n", [(torch.int32, 4000, 4000, 50_000), (torch.uint8, 2000, 2001, 50_000)])
+def test_gather_of_rows_that_are_not_staged(dtype, F, ld, n):
+    """Every selected element is a cache line of its own (128 bytes)."""
+    k = 20
+    x = torch.zeros((n, ld), dtype=dtype, device=DEV)[:, :F]
+    idx = torch.arange(k, dtype=torch.int32, device=DEV) * (F // k)
+    out = torch.empty((n, k), dtype=dtype, device=DEV)
+    lines = torch.zeros(n * min(k * 128, ld * x.element_size() // 16 * 16), dtype=torch.uint8, device=DEV)
+    sink = torch.empty(nbg.load().nb_probe_sink_words(), dtype=torch.int32, device=DEV)
+    gather, read = _us(lambda: nbg.gather_features(x, idx, out=out), lambda: nbg.probe_read(lines, sink))
+    print(f"[time] gather {gather:.1f} us, read of its lines {read:.1f} us", flush=True)
+    assert gather < 1.7 * read
