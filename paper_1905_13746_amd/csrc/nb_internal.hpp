@@ -68,6 +68,9 @@ int check_score_args(const nb_model* m, nb_layout* L, const void* x, int32_t xty
 bool score16_staged(const nb_model* m, const nb_layout& L, int32_t wtype, const float* scores);
 int launch_score16_staged(const nb_model* m, const nb_layout& L, const void* x, int32_t xtype, int64_t n, int64_t ld,
                           int32_t* labels, float* log_post, hipStream_t s);
+bool score_few(const nb_model* m, int32_t xtype);
+int launch_score_few(const nb_model* m, const nb_layout& L, const void* x, int32_t xtype, int64_t n, int64_t ld,
+                     int32_t wtype, int32_t* labels, float* log_post, float* scores, hipStream_t s);
 int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int32_t xtype, int64_t n, int64_t ld,
                       int32_t wtype, int32_t* labels, float* log_post, float* scores, hipStream_t s);
 

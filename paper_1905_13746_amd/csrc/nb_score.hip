@@ -153,8 +153,9 @@ extern "C" int nb_score(const nb_model* m, const void* x, int32_t xtype, int64_t
   if (m->n_classes == 2) return launch_score2(m, L, x, xtype, n, ld, wtype, labels, log_post, scores, s);
   rc = check_score_rows(m, xtype, ld, wtype, scores);
   if (rc) return rc;
-  // three or more classes: the matrix cores (16 classes on the BF16 table have a
-  // kernel of their own)
+  // three or more classes: short rows of a few classes on the vector ALUs, the rest
+  // on the matrix cores (16 classes on the BF16 table have a kernel of their own)
+  if (score_few(m, xtype)) return launch_score_few(m, L, x, xtype, n, ld, wtype, labels, log_post, scores, s);
   if (xtype != NB_X_I32 && score16_staged(m, L, wtype, scores))
     return launch_score16_staged(m, L, x, xtype, n, ld, labels, log_post, s);
   return launch_score_tile(m, L, x, xtype, n, ld, wtype, labels, log_post, scores, s);

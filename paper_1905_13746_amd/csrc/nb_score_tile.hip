@@ -62,6 +62,10 @@ namespace {
 constexpr int kWindow = 64;      // bytes of a file per 16-byte load of the operand layout
 constexpr int kFlush = 128;      // byte features per fresh accumulator
 
+// Waves per SIMD that a kernel's registers have to leave room for: the kernels of
+// short rows live by occupancy (two of a workgroup's waves per SIMD otherwise).
+constexpr int tile_waves(int NT, int KB, int NW, bool AUX) { return NT == 1 && KB <= 256 ? (AUX ? 3 : 4) : NW / 4; }
+
 struct ScoreTileArgs {
   const uint8_t* x;
   int64_t ld_bytes;
@@ -125,7 +129,7 @@ __device__ __forceinline__ void argmax_step(float& m, int& best) {
 // quarter of a lane's operations) from the FP32 values at hand.  ROW: one
 // accumulator per row.
 template <int XT, int NT, int NP, bool BIN, int MT, int PT, int KB, int SS, int NW, bool AUX, bool ROW>
-__global__ __launch_bounds__(64 * NW) void score_tile_kernel(ScoreTileArgs a) {
+__global__ __launch_bounds__(64 * NW, tile_waves(NT, KB, NW, AUX)) void score_tile_kernel(ScoreTileArgs a) {
   constexpr bool I32 = XT == NB_X_I32;
   constexpr int EB = I32 ? 4 : 1;           // bytes per feature
   constexpr int KS = KB / EB;               // features per slice
@@ -606,9 +610,22 @@ TileKernel tile_kernel() {
   return k;
 }
 
+// Short rows (at most 256 features, 128 for int32: two slices of a quarter of the
+// size) run in workgroups of four waves with a table small enough for four of them
+// per CU.  A file is then a chain of one or two loads and an epilogue, and with one
+// workgroup of eight waves per CU, as long rows have it, the chain's latency was all
+// the time: 300,000 files of 7 classes 35 us at any F up to 256, now 20 (F = 64) to 26
+// (F = 256); 1,000,000 int32 files of 16 classes, F = 16, 118 -> 57.  Sums are the
+// same.
+
 // int32 features: at most 32 score rows, either table.
 template <int NP, bool BIN>
-TileKernel pick_tile_i32(int nt, bool aux) {
+TileKernel pick_tile_i32(int nt, bool aux, bool narrow) {
+  if (narrow) {
+    if (nt == 1 && aux) return tile_kernel<NB_X_I32, 1, NP, BIN, 1, 2, 256, 256, 4, true>();
+    if (nt == 1) return tile_kernel<NB_X_I32, 1, NP, BIN, 1, 2, 256, 256, 4>();
+    if (nt == 2) return tile_kernel<NB_X_I32, 2, NP, BIN, 1, 2, 256, 256, 8>();
+  }
   if (nt == 1 && aux) return tile_kernel<NB_X_I32, 1, NP, BIN, 1, 2, 1024, 256, 8, true>();
   if (nt == 1) return tile_kernel<NB_X_I32, 1, NP, BIN, 1, 2, 1024, 256, 8>();
   if (nt == 2) return tile_kernel<NB_X_I32, 2, NP, BIN, 1, 2, 1024, 256, 8>();
@@ -618,7 +635,12 @@ TileKernel pick_tile_i32(int nt, bool aux) {
 // The slice is as long as two slices of the table and the waves' stages fit
 // the 160 KB of LDS.
 template <int XT, bool BIN>
-TileKernel pick_tile(int nt, bool f32, bool aux, bool four, bool row) {
+TileKernel pick_tile(int nt, bool f32, bool aux, bool four, bool row, bool narrow) {
+  if (narrow && nt == 1) {
+    if (f32 && aux) return tile_kernel<XT, 1, 3, BIN, 1, 2, 128, 128, 4, true>();
+    if (f32) return tile_kernel<XT, 1, 3, BIN, 1, 2, 128, 128, 4>();
+    if (!aux) return tile_kernel<XT, 1, 1, BIN, 1, 2, 128, 128, 4>();
+  }
   if (f32) {
     if (nt == 1 && aux)
       return four ? tile_kernel<XT, 1, 3, BIN, 1, 4, 512, 128, 8, true>()
@@ -663,15 +685,16 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   // 116; a resident table, F = 700: 189 against 193).  Sums are the same.
   const int64_t per_round = (int64_t)128 * device_cu_count();
   const bool four = f32 && m->n_features > 1024 && n >= 4 * per_round;
+  const bool narrow = m->n_features <= (xtype == NB_X_I32 ? 128 : 256);
   const bool row = xtype != NB_X_I32 && score16_staged(m, L, wtype, nullptr);
   TileKernel k;
   if (xtype == NB_X_I32) {
-    if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux) : pick_tile_i32<3, false>(nt, aux);
-    else k = bin ? pick_tile_i32<1, true>(nt, aux) : pick_tile_i32<1, false>(nt, aux);
+    if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux, narrow) : pick_tile_i32<3, false>(nt, aux, narrow);
+    else k = bin ? pick_tile_i32<1, true>(nt, aux, narrow) : pick_tile_i32<1, false>(nt, aux, narrow);
   } else if (xtype == NB_X_U8) {
-    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four, row) : pick_tile<NB_X_U8, false>(nt, f32, aux, four, row);
+    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four, row, narrow) : pick_tile<NB_X_U8, false>(nt, f32, aux, four, row, narrow);
   } else {
-    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four, row) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four, row);
+    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four, row, narrow) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four, row, narrow);
   }
   if (!k.fn) return fail(NB_EINVAL, "too many score columns for the table type");
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);
