@@ -123,7 +123,7 @@ __device__ __forceinline__ void argmax_step(float& m, int& best) {
 // NT: 16-class column tiles.  NP: BF16 parts of a table entry (3: FP32 table,
 // 1: BF16 table; int32 features: entries are staged in FP32 from either).  MT:
 // 16-file tiles of a unit.  PT: units per wave of a wide workgroup tile (even:
-// the two load buffers alternate).  KB: bytes per file of a slice.  SS: bytes per
+// the two load buffers alternate), or 1: no wide tiles.  KB: bytes per file of a slice.  SS: bytes per
 // file of the stage.  NW: waves.  AUX: the raw scores' aux row, which would need a column
 // tile of its own, is contracted on the vector ALUs (one FMA per byte, a
 // quarter of a lane's operations) from the FP32 values at hand.  ROW: one
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * NW, tile_waves(NT, KB, NW, AUX)) void score_ti
   constexpr int KS = KB / EB;               // features per slice
   constexpr int WF = kWindow / EB;          // features per window
   static_assert(!ROW || (NP == 1 && !I32), "one accumulator");
-  static_assert(PT % 2 == 0 && SS % kFlush == 0 && KB % SS == 0 && 1024 % KB == 0, "tile shape");
+  static_assert((PT == 1 || PT % 2 == 0) && SS % kFlush == 0 && KB % SS == 0 && 1024 % KB == 0, "tile shape");
   constexpr int kThreads = 64 * NW;
   constexpr int GF = 16 * MT;               // files per unit
   constexpr int NG = SS / 16;               // granules per file of the stage
@@ -356,42 +356,51 @@ __global__ __launch_bounds__(64 * NW, tile_waves(NT, KB, NW, AUX)) void score_ti
                 acc[0][mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[mt][e], __uint_as_float(bv[nt][e]),
                                                                       acc[0][mt][nt], 0, 0, 0);
         } else {
-          dev::u32x4 bv[NT][2][NP];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-              for (int part = 0; part < NP; ++part)
-                bv[nt][h][part] = (tb + tpos[u % 2][h])[part * kPart + 16 * nt * GPR + u / 2 * 16];
+          // column tiles in groups whose operands the registers hold beside the sums
+          // (16 tiles at two waves per SIMD)
+          constexpr int kGroup = NT > 8 && PT == 1 ? 4 : NT;
           dev::u32x4 av[MT][2];
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            const int f0 = s * KS + u * kWindow + 16 * q;
-            if (XT == NB_X_FP8 && f0 + 16 > a.F) {   // NaN encodings past the last feature
-              const int nv = max(0, a.F - f0);
+          for (int n0 = 0; n0 < NT; n0 += kGroup) {
+            dev::u32x4 bv[kGroup][2][NP];
 #pragma unroll
-              for (int d = 0; d < 4; ++d) {
-                const int nb = min(4, max(0, nv - 4 * d));
-                xv[mt][d] &= (nb >= 4) ? ~0u : ((1u << (8 * nb)) - 1u);
-              }
-            }
-            float g[16];
-            to_bf16<XT, BIN>(xv[mt], av[mt][0], av[mt][1], g);
-            if constexpr (AUX) add_aux(mt, u * kWindow + 16 * q, g, 16);
-          }
-          if ((u + 1) % (SS / kWindow) != 0) read_window(u + 1);
+            for (int nt = 0; nt < kGroup; ++nt)
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
+              for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+                for (int part = 0; part < NP; ++part)
+                  bv[nt][h][part] = (tb + tpos[u % 2][h])[part * kPart + 16 * (n0 + nt) * GPR + u / 2 * 16];
+            if (n0 == 0) {
 #pragma unroll
-              for (int part = 0; part < NP; ++part)
+              for (int mt = 0; mt < MT; ++mt) {
+                const int f0 = s * KS + u * kWindow + 16 * q;
+                if (XT == NB_X_FP8 && f0 + 16 > a.F) {   // NaN encodings past the last feature
+                  const int nv = max(0, a.F - f0);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                  f32x4& c = acc[part == 0 ? 0 : kAcc - 1][mt][nt];
-                  c = mfma(av[mt][h], bv[nt][h][part], c);
+                  for (int d = 0; d < 4; ++d) {
+                    const int nb = min(4, max(0, nv - 4 * d));
+                    xv[mt][d] &= (nb >= 4) ? ~0u : ((1u << (8 * nb)) - 1u);
+                  }
                 }
+                float g[16];
+                to_bf16<XT, BIN>(xv[mt], av[mt][0], av[mt][1], g);
+                if constexpr (AUX) add_aux(mt, u * kWindow + 16 * q, g, 16);
+              }
+              if ((u + 1) % (SS / kWindow) != 0) read_window(u + 1);
+            }
+#pragma unroll
+            for (int nt = 0; nt < kGroup; ++nt)
+#pragma unroll
+              for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int part = 0; part < NP; ++part)
+#pragma unroll
+                  for (int mt = 0; mt < MT; ++mt) {
+                    f32x4& c = acc[part == 0 ? 0 : kAcc - 1][mt][n0 + nt];
+                    c = mfma(av[mt][h], bv[nt][h][part], c);
+                  }
+            if (n0 + kGroup < NT) __builtin_amdgcn_sched_barrier(0);
+          }
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -524,27 +533,29 @@ __global__ __launch_bounds__(64 * NW, tile_waves(NT, KB, NW, AUX)) void score_ti
 
   // ---- wide tiles: PT units per wave and slice, every load in bounds; unit p
   // of wave w starts at file ((tile PT + p) NW + w) GF
-  auto wide_row = [&](int64_t tile, int p) { return ((tile * PT + p) * NW + wave) * GF; };
-  if ((int64_t)blockIdx.x < a.wide_tiles) issue(wide_row(blockIdx.x, 0), 0, buf[0]);
-  for (int64_t tile = blockIdx.x; tile < a.wide_tiles; tile += gridDim.x) {
-    f32x4 tot[PT][MT][NT];
-    float taux[PT][MT] = {};
+  if constexpr (PT > 1) {
+    auto wide_row = [&](int64_t tile, int p) { return ((tile * PT + p) * NW + wave) * GF; };
+    if ((int64_t)blockIdx.x < a.wide_tiles) issue(wide_row(blockIdx.x, 0), 0, buf[0]);
+    for (int64_t tile = blockIdx.x; tile < a.wide_tiles; tile += gridDim.x) {
+      f32x4 tot[PT][MT][NT];
+      float taux[PT][MT] = {};
 #pragma unroll
-    for (int p = 0; p < PT; ++p) zero(tot[p]);
-    const int64_t next = tile + gridDim.x < a.wide_tiles ? tile + gridDim.x : tile;   // after the last: a re-read
-    for (int s = 0; s < nsl; ++s) {
-      const int sn = s + 1 < nsl ? s + 1 : 0;
-      begin_slice(sn);
+      for (int p = 0; p < PT; ++p) zero(tot[p]);
+      const int64_t next = tile + gridDim.x < a.wide_tiles ? tile + gridDim.x : tile;   // after the last: a re-read
+      for (int s = 0; s < nsl; ++s) {
+        const int sn = s + 1 < nsl ? s + 1 : 0;
+        begin_slice(sn);
 #pragma unroll
-      for (int p = 0; p < PT; ++p) {
-        if (p + 1 < PT) issue(wide_row(tile, p + 1), s, buf[(p + 1) & 1]);
-        else issue(wide_row(sn ? tile : next, 0), sn, buf[0]);
-        compute(s, cur, buf[p & 1], tot[p], taux[p]);
+        for (int p = 0; p < PT; ++p) {
+          if (p + 1 < PT) issue(wide_row(tile, p + 1), s, buf[(p + 1) & 1]);
+          else issue(wide_row(sn ? tile : next, 0), sn, buf[0]);
+          compute(s, cur, buf[p & 1], tot[p], taux[p]);
+        }
+        end_slice(sn);
       }
-      end_slice(sn);
-    }
 #pragma unroll
-    for (int p = 0; p < PT; ++p) finish(wide_row(tile, p), tot[p], taux[p]);
+      for (int p = 0; p < PT; ++p) finish(wide_row(tile, p), tot[p], taux[p]);
+    }
   }
 
   // ---- the remaining files, one unit per wave and tile; units that reach the
@@ -634,8 +645,13 @@ TileKernel pick_tile_i32(int nt, bool aux, bool narrow) {
 
 // The slice is as long as two slices of the table and the waves' stages fit
 // the 160 KB of LDS.
+//
+// 129 to 256 score rows: the sums of two units take the registers of a wave per SIMD,
+// so a call of more files than such waves hold (small: one unit each) takes one unit
+// per wave and two waves per SIMD (200 classes, F = 1000, 30,000 files: 94 -> 38 us;
+// 10,000 FP8 files at F = 4096 84 against 122).
 template <int XT, bool BIN>
-TileKernel pick_tile(int nt, bool f32, bool aux, bool four, bool row, bool narrow) {
+TileKernel pick_tile(int nt, bool f32, bool aux, bool four, bool row, bool narrow, bool small) {
   if (narrow && nt == 1) {
     if (f32 && aux) return tile_kernel<XT, 1, 3, BIN, 1, 2, 128, 128, 4, true>();
     if (f32) return tile_kernel<XT, 1, 3, BIN, 1, 2, 128, 128, 4>();
@@ -659,7 +675,8 @@ TileKernel pick_tile(int nt, bool f32, bool aux, bool four, bool row, bool narro
     case 3: return tile_kernel<XT, 3, 1, BIN, 1, 2, 512, 512, 8>();
     case 4: return tile_kernel<XT, 4, 1, BIN, 1, 2, 256, 256, 8>();
     case 8: return tile_kernel<XT, 8, 1, BIN, 1, 2, 256, 128, 8>();
-    case 16: return tile_kernel<XT, 16, 1, BIN, 1, 2, 128, 128, 4>();
+    case 16:
+      return small ? tile_kernel<XT, 16, 1, BIN, 1, 2, 128, 128, 4>() : tile_kernel<XT, 16, 1, BIN, 1, 1, 128, 128, 8>();
     default: return {};
   }
 }
@@ -686,15 +703,16 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   const int64_t per_round = (int64_t)128 * device_cu_count();
   const bool four = f32 && m->n_features > 1024 && n >= 4 * per_round;
   const bool narrow = m->n_features <= (xtype == NB_X_I32 ? 128 : 256);
+  const bool small = n <= (int64_t)64 * device_cu_count();
   const bool row = xtype != NB_X_I32 && score16_staged(m, L, wtype, nullptr);
   TileKernel k;
   if (xtype == NB_X_I32) {
     if (f32) k = bin ? pick_tile_i32<3, true>(nt, aux, narrow) : pick_tile_i32<3, false>(nt, aux, narrow);
     else k = bin ? pick_tile_i32<1, true>(nt, aux, narrow) : pick_tile_i32<1, false>(nt, aux, narrow);
   } else if (xtype == NB_X_U8) {
-    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four, row, narrow) : pick_tile<NB_X_U8, false>(nt, f32, aux, four, row, narrow);
+    k = bin ? pick_tile<NB_X_U8, true>(nt, f32, aux, four, row, narrow, small) : pick_tile<NB_X_U8, false>(nt, f32, aux, four, row, narrow, small);
   } else {
-    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four, row, narrow) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four, row, narrow);
+    k = bin ? pick_tile<NB_X_FP8, true>(nt, f32, aux, four, row, narrow, small) : pick_tile<NB_X_FP8, false>(nt, f32, aux, four, row, narrow, small);
   }
   if (!k.fn) return fail(NB_EINVAL, "too many score columns for the table type");
   const uint8_t* base = static_cast<const uint8_t*>(m->dev);
@@ -726,7 +744,8 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   const int64_t wide_fit = a.nfast / (per_tile * k.units);       // wide tiles with every load in bounds
   const int64_t rounds = tiles / (cap * k.units);
   const int64_t rest = tiles - rounds * cap * k.units;
-  a.wide_tiles = std::min(wide_fit, rest > cap * (k.units - 1) ? (rounds + 1) * cap : rounds * cap);
+  a.wide_tiles =
+      k.units == 1 ? 0 : std::min(wide_fit, rest > cap * (k.units - 1) ? (rounds + 1) * cap : rounds * cap);
   const int64_t want = std::max(a.wide_tiles, tiles - a.wide_tiles * k.units);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min(want, cap));
   hipLaunchKernelGGL(k.fn, dim3(grid), dim3(64 * k.waves), k.lds, s, a);

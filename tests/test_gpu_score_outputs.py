@@ -52,3 +52,23 @@ def test_nan_features(C, wtype, scores):
     good[bad] = False
     assert torch.isnan(lp[bad]).all() and (lab[bad] == 0).all()
     assert torch.equal(lp[good], want[1][good]) and torch.equal(lab[good], want[0][good])
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("C,F", [(129, 60), (200, 388), (255, 132)])
+def test_many_classes_many_files_equal_small_calls(C, F, fp8):
+    """More than 128 score rows: another kernel for more files than a unit per wave."""
+    print(f"[case] many classes C={C} F={F} fp8={fp8}", flush=True)
+    n, base = 40_005, 1999
+    wl = W.Workload(wid=6, n_classes=C, n_features=F, p_zero=0.6, clip255=True, group=C * 512 + F)
+    X, y = wl.train_set(12 * C, device=DEV)
+    m = nbg.Model(C, F, "multinomial")
+    nbg.train(m, X, y)
+    T, _ = wl.test_set(base, device=DEV)
+    x = W.to_fp8_e4m3(T) if fp8 else T
+    want = nbg.score(m, x, wtype=nbg.W_BF16, fp8=fp8, scores=True)
+    at = torch.arange(n, device=DEV) % base
+    pad = torch.full((n, F + 4), 0x7F, dtype=torch.uint8, device=DEV)
+    pad[:, :F] = x[at]
+    for u, v in zip(nbg.score(m, pad[:, :F], wtype=nbg.W_BF16, fp8=fp8, scores=True), want):
+        assert torch.equal(u, v[at])
