@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kThreads, XT == NB_X_I32 || SQ ? 2 : 3) void count_
 #pragma unroll
           for (int q = 0; q < NV; ++q) {
             const int64_t off = (int64_t)rel[k] * a.ld_bytes + col[q];
-            if (live[q] && off + 16 > (int64_t)end)
+            if (k < cnt && live[q] && off + 16 > (int64_t)end)
               v[k][q] = dev::load16_guarded(a.x + base * a.ld_bytes + off, left - off);
           }
       }

@@ -62,3 +62,19 @@ def test_short_rows_of_a_few_classes(C, F, factor):
 
 def test_many_classes():
     _score_against_read(200, 1000, 30_000, nbg.W_BF16, 7.0)
+
+
+def test_training_reads_the_last_row_once():
+    """The row that ends the buffer is read byte by byte; where it is alone in its batch
+    (1,000 files) the batch's empty places must not read it again."""
+    C, F = 7, 1000
+    calls = []
+    for n in (1000, 1008):
+        x = torch.ones((n, F), dtype=torch.uint8, device=DEV)
+        y = (torch.arange(n, device=DEV) % C).to(torch.int32)
+        m = nbg.Model(C, F, "bernoulli")
+        ws = nbg.train_workspace(m, n)
+        calls.append(lambda m=m, x=x, y=y, ws=ws: nbg.train(m, x, y, workspace=ws, asynchronous=True))
+    alone, beside = _us(*calls)
+    print(f"[time] training {alone:.1f} us, with a fuller last batch {beside:.1f} us", flush=True)
+    assert alone < 1.15 * beside
