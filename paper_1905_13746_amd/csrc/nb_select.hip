@@ -594,7 +594,7 @@ int nb_gather_features(const void* x, int32_t xtype, int64_t n, int32_t F, int64
     auto pick = [&]() { return (es == 1) ? pick_gather<1>(nl, (int)rw, q) : pick_gather<4>(nl, (int)rw, q); };
     auto launched = [&]() {
       return gather_workgroups(resident_per_cu(pick(), kGatherThreads, lds), 100,
-                               2 * rw * (a.ld_bytes + 2 * (int64_t)k * es));
+                               2 * ((rw - 1) * a.ld_bytes + a.row_bytes + 2 * rw * (int64_t)k * es));
     };
     // no fewer units than waves launched for them
     while (rw > 1 && (n + rw - 1) / rw < launched() * device_cu_count() * kGatherWaves) rw /= 2;
