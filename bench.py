@@ -325,7 +325,7 @@ def precision_compare(nbg, W, fill: bool = False):
         lab = torch.empty(n, dtype=torch.int32, device="cuda")
         lp = torch.empty((n, C), dtype=torch.float32, device="cuda")
         res = {"workload": f"{C} classes, F={F}, {n} constant-filled files (counter run)"}
-        for name, kw in (("fp32_vector", {"wtype": 0}), ("bf16_mfma_u8", {"wtype": 1})):
+        for name, kw in (("fp32_mfma_u8", {"wtype": 0}), ("bf16_mfma_u8", {"wtype": 1})):
             ms = timed(lambda: nbg.score(m, Xt, out=(lab, lp, None), **kw), 3)
             res[name] = {"ms": ms, "GBps": n * (F + 4 + 4 * C) / (ms / 1e3) / 1e9}
         return res
@@ -350,18 +350,18 @@ def precision_compare(nbg, W, fill: bool = False):
                        "labels of the three paths compared on every file",
            "n_files": n, "train": train}
     labels = {}
-    for name, x, kw in (("fp32_vector", Xt, {"wtype": 0}), ("bf16_mfma_u8", Xt, {"wtype": 1}),
+    for name, x, kw in (("fp32_mfma_u8", Xt, {"wtype": 0}), ("bf16_mfma_u8", Xt, {"wtype": 1}),
                         ("bf16_mfma_fp8", q8, {"wtype": 1, "fp8": True})):
         ms = timed(lambda: nbg.score(m, x, out=(lab, lp, None), **kw))
         labels[name] = lab.clone()
         gbs = n * (F + 4 + 4 * C) / (ms / 1e3) / 1e9
         res[name] = {"ms": ms, "files_per_s": n / (ms / 1e3), "GBps": gbs, "frac_of_peak": gbs / HBM_PEAK_GBPS}
-    res["bf16_vs_fp32_labels_identical_all_files"] = float((labels["bf16_mfma_u8"] == labels["fp32_vector"])
+    res["bf16_vs_fp32_labels_identical_all_files"] = float((labels["bf16_mfma_u8"] == labels["fp32_mfma_u8"])
                                                             .float().mean().item())
-    res["fp8_vs_fp32_labels_identical_all_files"] = float((labels["bf16_mfma_fp8"] == labels["fp32_vector"])
+    res["fp8_vs_fp32_labels_identical_all_files"] = float((labels["bf16_mfma_fp8"] == labels["fp32_mfma_u8"])
                                                            .float().mean().item())
-    res["speedup_bf16_u8_vs_fp32"] = res["fp32_vector"]["ms"] / res["bf16_mfma_u8"]["ms"]
-    res["speedup_bf16_fp8_vs_fp32"] = res["fp32_vector"]["ms"] / res["bf16_mfma_fp8"]["ms"]
+    res["speedup_bf16_u8_vs_fp32"] = res["fp32_mfma_u8"]["ms"] / res["bf16_mfma_u8"]["ms"]
+    res["speedup_bf16_fp8_vs_fp32"] = res["fp32_mfma_u8"]["ms"] / res["bf16_mfma_fp8"]["ms"]
     res["error_vs_oracle"] = error_vs_oracle()
     return res
 
@@ -825,7 +825,7 @@ def compact(leg: str, res: dict) -> dict:
                 for k, v in res.items()}
     if leg == "precision":
         out = {k: {"ms": r3(res[k]["ms"]), "frac_of_peak": r3(res[k]["frac_of_peak"])}
-               for k in ("fp32_vector", "bf16_mfma_u8", "bf16_mfma_fp8")}
+               for k in ("fp32_mfma_u8", "bf16_mfma_u8", "bf16_mfma_fp8")}
         if "train" in res:
             out["train_16class"] = {"ms": r3(res["train"]["ms"]),
                                     "frac_of_peak": r3(res["train"]["GBps"] / HBM_PEAK_GBPS)}

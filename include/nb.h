@@ -175,7 +175,7 @@ int nb_model_status(nb_model* model, void* stream);
  * accumulation is FP32.  Outputs (device, any may be NULL but not all):
  *   labels int32[n], log_post float[n x C], scores float[n x C] (raw s_c).
  * n == 0 is a no-op.  The per-file summation order depends only on (F, C,
- * xtype, wtype), never on n or on other files.
+ * xtype, wtype), never on n, on the outputs requested or on other files.
  * Gaussian models: s_c = bias_c + sum_f h_cf (x_f - mean_cf)^2 (the density's
  * own form: no large terms cancel when a variance is tiny), two classes,
  * uint8 or int32 features, F up to 8192. */

@@ -101,8 +101,10 @@ int launch_score2(const nb_model* m, const nb_layout& L, const void* x, int32_t 
 }
 
 // Limits of the paths for more than two classes: the FP32 table and int32
-// features take 32 score rows, byte features on the BF16 table 256, and the rows
-// that one resource descriptor spans must stay below 2 GiB.
+// features take 32 score rows, byte features on the BF16 table 256.  Row strides
+// are refused where 64 rows (128 or 256 of 16 and more classes on the BF16 table)
+// span 2 GiB; a resource descriptor of these kernels spans at most 64 rows, so every
+// stride that is taken lies within its 32-bit offsets.
 int check_score_rows(const nb_model* m, int32_t xtype, int64_t ld, int32_t wtype, const float* scores) {
   const int ns = m->n_classes + (scores ? 1 : 0);
   const bool few = wtype == NB_W_F32 || m->n_classes < 16 || xtype == NB_X_I32;

@@ -1,7 +1,8 @@
 // Naive Bayes scoring of 16 classes with a BF16 table, labels and log
 // posteriors, on the matrix cores: the benchmark's precision configuration.
-// The general kernel (nb_score_tile.hip) serves every other class count, the
-// FP32 table and raw scores; here the whole table stays in LDS, which keeps the
+// The general kernel (nb_score_tile.hip) serves every other class count (but for
+// short rows of a few classes, nb_score_few.hip), the FP32 table and raw scores; here
+// the whole table stays in LDS, which keeps the
 // wave's load stream free of table slices and barriers: 360 against 368-376 us
 // for 500,000 FP8 files at F = 4096, 191 against 196-200 us for 800,000 byte
 // files at F = 1000.

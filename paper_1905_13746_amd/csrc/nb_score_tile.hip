@@ -1,6 +1,8 @@
 // Naive Bayes scoring for more than two classes on the matrix cores (paper,
 // section 4: the class with the highest posterior wins; here C >= 3, e.g. malware
-// families), with the FP32 or the BF16 table.
+// families), with the FP32 or the BF16 table (short rows of a few classes run in
+// nb_score_few.hip, 16 classes on the BF16 table without raw scores in
+// nb_score_mfma.hip).
 //
 // s[file, class] = sum_f g(x_f) W[class, f] is a skinny GEMM (M = files, N =
 // classes, K = features).  Byte counts and FP8-e4m3 values are exact in BF16.
@@ -14,11 +16,12 @@
 // features go through v_mfma_f32_16x16x4_f32 (FP32 products and sums, a third of
 // the matrix cores' time at that rate), four of them per 16-byte load.
 //
-// What bounds it is HBM, and the LDS behind it: 16 files share each table read,
-// so the FP32 table's three parts cost 6 bytes of LDS traffic per feature byte
-// beside the 2 of the transpose (of about 13 per byte that the CUs' LDS delivers
-// at 6 TB/s); 32 files per unit halve that but leave one wave per SIMD the
-// registers, and measured slower (415 against 345 us).  A wave's unit is 16
+// What bounds it is HBM and, with the FP32 table, the waits that two waves per SIMD
+// leave open.  Counters of 4,000,000 files of 16 classes, F = 4096 (5.4 TB/s, HBM
+// traffic 1.001 x): vector ALUs busy 44% of the cycles, LDS 36% without a bank
+// conflict, matrix cores 22%; a wave waits for 29% of its time, for 7% on LDS.  16 files
+// share each table read; 32 files per unit halve the LDS traffic but leave one wave
+// per SIMD the registers, and measured slower (415 against 345 us).  A wave's unit is 16
 // files x KB bytes, loaded as KB contiguous bytes of each file (512 where the
 // table leaves room: 256-byte runs took 415 us for the same files), one unit
 // ahead in registers, and transposed through the wave's private LDS stage, SS
@@ -28,19 +31,20 @@
 // staged once per 16 PT files of each of its waves.  A table of at most two
 // slices stays in LDS and the waves run without barriers.
 //
-// Measured (us; byte features but for the last three; before: vector ALUs for
-// the FP32 table, int32 features and fewer than 16 classes, a matrix-core kernel
-// on 64-byte loads for the rest):
-//   FP32, 16 classes, F = 4096, 400,003 files        1,718 ->  354  (4.6 TB/s)
-//   the same with raw scores                         1,980 ->  363
-//   FP32, 20 classes, F = 2000, 300,000 files          905 ->  204
-//   FP32, 7 classes, F = 1000, 600,000 files           347 ->  152
-//   FP32, 16 classes, F = 1000, 2,000 files            128 ->   13
-//   BF16, 40 classes, F = 1000, 400,001 files, scores  214 ->  127
-//   BF16, 100 classes, F = 2000, 150,000 files         354 ->  154
-//   int32, 7 classes, F = 2964, 67,476 files, scores   645 ->  230
-//   int32, 16 classes, F = 1792, 111,607 files         484 ->  180
-//   int32, 24 classes, F = 1000, 100,000 files         887 ->  158
+// Measured (us; byte features but for the last three), beside the other design
+// tried for each: one file per lane on the vector ALUs for the FP32 table and int32
+// features, matrix cores on 64-byte loads without a stage for the BF16 table.
+//                                                     other   this
+//   FP32, 16 classes, F = 4096, 400,003 files         1,718    354  (4.6 TB/s)
+//   the same with raw scores                          1,980    362
+//   FP32, 20 classes, F = 2000, 300,000 files           905    204
+//   FP32, 7 classes, F = 1000, 600,000 files            347    152
+//   FP32, 16 classes, F = 1000, 2,000 files             128     13
+//   BF16, 40 classes, F = 1000, 400,001 files, scores   214    127
+//   BF16, 100 classes, F = 2000, 150,000 files          354    154
+//   int32, 7 classes, F = 2964, 67,476 files, scores    645    230
+//   int32, 16 classes, F = 1792, 111,607 files          484    180
+//   int32, 24 classes, F = 1000, 100,000 files          887    158
 //
 // Sums: the products of 128 consecutive features (16 int32 ones) go to fresh
 // accumulators (leading parts and lower parts apart), whose sum is added to the
@@ -695,11 +699,17 @@ int launch_score_tile(const nb_model* m, const nb_layout& L, const void* x, int3
   const bool f32 = wtype == NB_W_F32, bin = m->kind == NB_BERNOULLI;
   const bool aux = scores && C == 16;      // 16 classes fill the tile: the aux row would need a second one
   const int nt = aux ? 1 : round_nt((ns + 15) / 16);
-  // Four units per wave and slice where the FP32 table does not stay in LDS and
-  // every workgroup gets four (its slices are then staged half as often: 16
-  // classes, raw scores, F = 4096, 400,003 files 379 us with two, 362 with four);
-  // two otherwise (90,000 files: 100 us, where four leave only single-unit tiles,
-  // 116; a resident table, F = 700: 189 against 193).  Sums are the same.
+  // Four units per wave and slice for the FP32 table of 16 classes with raw scores
+  // and of 17 to 32 score rows, from 1,025 features (its slices, which do not stay in
+  // LDS, are then staged half as often) and from four units for every workgroup: 16
+  // classes, raw scores, F = 4096, 400,003 files 379 us with two, 362 with four; 90,000
+  // files 100 us, where four leave only single-unit tiles, 116; a resident table, F =
+  // 700, 189 against 193.  Two elsewhere: one column tile without the aux row differs
+  // less (16 classes, F = 2000, 400,000 files 211 us with two, 204 with four; 3
+  // classes, F = 4096, 200,000 files 191 and 195), and so do 17 to 32 rows of 513 to
+  // 1,024 features, whose slices are half as long (20 classes, 300,000 files, F =
+  // 1000: 119 and 112; 31 classes, 1,000,000 files, F = 800: 307 both).  Sums are the
+  // same.
   const int64_t per_round = (int64_t)128 * device_cu_count();
   const bool four = f32 && m->n_features > 1024 && n >= 4 * per_round;
   const bool narrow = m->n_features <= (xtype == NB_X_I32 ? 128 : 256);

@@ -85,7 +85,10 @@ struct CountArgs {
 // byte features (a flush comes every 256 rows, long before they can wrap), int64
 // for int32 features (values of 65536 or more are flagged: their squares could
 // overflow the exact int64 sums).  One pass for both sums takes 36 us where
-// two passes took 35 us each (200,000 files, F = 1000).
+// two passes took 35 us each (200,000 files, F = 1000).  Whole calls, one pass and
+// two: 200,000 byte files of 7 classes 98 and 164 us; int32, F = 1000, 200,000 files 179
+// and 346 us (2 classes) and 232 and 591 (7), though the int64 sums of both moments
+// leave the int32 kernels 15 to 49 registers short.
 //
 // WIN: 64-row label windows whose matching rows are loaded together.  With
 // WIN = 1 the rows of a batch come straight from the window's ballot mask;
@@ -1131,12 +1134,15 @@ int count_capacity(int32_t xtype, int win, bool sq) {
 // Two classes: as many (slot, class, chunk) workgroups as fit on the device
 // in one round (a few more would run as a second, nearly empty round).  With
 // more classes a workgroup's work is the rows of its class in its slot, which
-// differs between classes as much as their priors do; four rounds of smaller
-// slots let the workgroups of the small classes finish and make room, so that
-// the large classes' rows are spread over the device, and whole row lists of
+// differs between classes as much as their priors do; up to four rounds of
+// smaller slots let the workgroups of the small classes finish and make room, so
+// that the large classes' rows are spread over the device, and whole row lists of
 // the four waves per slot keep the loads in full batches (16 classes, F = 4096,
 // 200,003 files: 247 -> 239 us; two classes lose by it, 49.5 -> 55.0 us, the
-// longer slots leaving workgroups out).
+// longer slots leaving workgroups out).  Rounding the rows up to whole lists leaves
+// between two and four rounds: 16 even classes at F = 4096 take 48 slots (four
+// rounds) and 144 us of counting for 196,608 files, 25 slots (2.1 rounds) and 148 us
+// for 200,003.
 constexpr int64_t kManyClassRounds = 4;
 struct Slots {
   int64_t rows, n;       // rows per slot, slots

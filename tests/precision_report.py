@@ -15,8 +15,8 @@ each result it returns:
     be 100%).
 Paths: two classes at F = 1000 (1,000,000 files; FP32 table, and the BF16
 table; on the headline workload and on near-tied classes, whose small
-margins populate the label band), sixteen classes at F = 4096 (4,000,000 files; the FP32 vector path,
-the BF16 matrix cores on uint8 and on FP8-e4m3 features).  FP8 features are
+margins populate the label band), sixteen classes at F = 4096 (4,000,000 files; the FP32 table and
+the BF16 table on the matrix cores, uint8 and FP8-e4m3 features).  FP8 features are
 compared two ways: against the oracle on the FP8 values the kernel was given
 (arithmetic error) and against the oracle on the original counts (total
 error), and the quantisation alone is stated as the oracle on q(x) against
@@ -221,7 +221,7 @@ def sixteen_class(n_test, n_train):
     Xt, _ = wl.test_set(n_test, device="cuda")
     q8 = nbg.quantize_fp8(Xt)
     paths = []
-    specs = (("FP32 table, vector ALUs, uint8", Xt, nbg.W_F32, False, False),
+    specs = (("FP32 table, matrix cores, uint8", Xt, nbg.W_F32, False, False),
              ("BF16 table, matrix cores, uint8", Xt, nbg.W_BF16, False, False),
              ("BF16 table, matrix cores, FP8-e4m3", q8, nbg.W_BF16, True, False),
              ("BF16 table, matrix cores, FP8-e4m3", q8, nbg.W_BF16, True, True))
